@@ -39,8 +39,7 @@ KERNEL_SOURCES = {"k_guide_stats": ["guide_scores.hip", "tile_common.h", "tp_int
                   "k_sel_score": ["select.hip", "tp_internal.h", "abi.cpp"],
                   "k_select": ["select.hip", "tp_internal.h", "abi.cpp"],
                   "k_compact": ["compact.hip", "tp_internal.h"],
-                  "k_compact_quant": ["compact.hip", "quant_row.h", "quant_recip_table.h", "tp_internal.h"],
-                  "k_lse_import": ["guide_scores.hip", "tile_common.h", "tp_internal.h"]}
+                  "k_compact_quant": ["compact.hip", "quant_row.h", "quant_recip_table.h", "tp_internal.h"]}
 
 
 def algorithmic_bytes(w, kept_total_per_head, full_codes=True, normalisers_given=False):
@@ -57,12 +56,11 @@ def algorithmic_bytes(w, kept_total_per_head, full_codes=True, normalisers_given
     kt = kept_total_per_head
     q_bytes = w.L * w.Hq * w.g_tot * d * 2
     rows = w.L * w.Hq * w.g_tot
-    chunk = 16384 if min(w.ctx_lens) >= 65536 else 8192  # the score passes' chunk (tp_internal.h)
+    chunk = 16384 if min(w.ctx_lens) >= 65536 else 8192  # the score passes' usual chunk (guide_scores.hip)
     nch = -(-max(w.ctx_lens) // chunk)
     per = {
         "k_guide_stats": LH * n * 2 * d + q_bytes + rows * nch * 8,     # read K, write chunk stats
         "k_guide_lse": rows * (nch * 8 + 4),                            # merge chunk stats
-        "k_lse_import": rows * 8,                                       # supplied normalisers -> log2
         "k_guide_attn": LH * n * (2 * d + 4) + q_bytes,                 # read K, write raw
         "k_guide_pool": LH * n * (4 + 4),                               # read raw, write s_key
         "k_quantize": LH * n * (2 * d + rb + 4),                        # read V, write codes and scales
@@ -445,13 +443,14 @@ def main():
     else:
         step_ms = sorted(e[0].elapsed_time(e[-1]) for e in evs)
     ms = statistics.median(step_ms)
-    stages = STAGES if lse is None else ["pass1_skipped", "k_lse_import"] + STAGES[2:]
+    stages = STAGES if lse is None else ["pass1_skipped", "lse_given"] + STAGES[2:]
     if args.no_full_codes:
         stages = stages[:-1] + ["k_compact_quant"]
     if w.rule == B.TP_COMBINE_NORM_ADD:  # its norms need the pooled scores first: a pooling kernel
         stages[4] = "k_guide_pool"
     stage_ms = {n: statistics.median(e[j].elapsed_time(e[j + 1]) for e in evs) for j, n in enumerate(stages)}
-    stage_ms.pop("pass1_skipped", None)
+    for none in ("pass1_skipped", "lse_given"):  # no kernel between these events
+        stage_ms.pop(none, None)
     if args.prefill_attention:  # step 2 ran inside the attention: no kernel between its events
         stage_ms.pop("k_quantize")
         stage_ms = dict({"k_guide_fwd": statistics.median(a[0].elapsed_time(a[1]) for a in atts)}, **stage_ms)
@@ -536,7 +535,7 @@ def main():
         "stages_ms": {n: round(t, 4) for n, t in stage_ms.items()},
         "kernel_rooflines": {n: {k: v for k, v in roofline_of(n).items()
                                  if k in ("bound", "achieved", "unit", "frac", "other_roof")}
-                             for n in stage_ms if n not in ("k_guide_lse", "k_lse_import")},
+                             for n in stage_ms if n != "k_guide_lse"},
     }
     del q, k, v, kg, vg, bufs, flush, ws_attn
     if not args.no_cpu_baseline:

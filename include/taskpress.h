@@ -299,8 +299,9 @@ tp_status tp_compact_quantize_kv(const tp_dims* dims, const tp_batch* batch, con
  * stream, in launch order: [0] before the work, [1] after score pass 1, [2] after the row
  * normalisers, [3] after the V quantisation, [4] after score pass 2, [5] after pooling,
  * [6] after the selection, [7] after the compaction; one kernel runs between consecutive
- * events (with guide_lse, none between [0] and [1], and [1]..[2] converts the supplied
- * normalisers).
+ * events, except that a step which needs no kernel has none: with guide_lse, none from [0] to
+ * [2]; in small calls, where score pass 2 merges the row normalisers itself, none between [1]
+ * and [2].
  * num_events = 0 (or a NULL profile) records none.
  */
 #define TP_EVICT_EVENTS 8

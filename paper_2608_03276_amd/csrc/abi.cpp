@@ -181,7 +181,7 @@ tp_status prepare_guide(const tp_dims* dims, const tp_batch* batch, const void* 
   a.c = (float)((double)softmax_scale * 1.4426950408889634);
   a.pool_inv = (float)(1.0 / ((double)a.R * pool_k));
   a.pool_half = pool_k / 2;
-  a.chunk = tp::chunk_tokens(batch->ctx_offsets, batch->batch);
+  a.chunk = lay.chunk;
   a.nchunk_max = (int32_t)((max_nb + a.chunk - 1) / a.chunk);
   a.nrg_max = (int32_t)((a.R * max_gb + tp::kRowsPerGroup - 1) / tp::kRowsPerGroup);
   // workgroups of the score passes (the launcher splits them into row-block classes, each
@@ -191,11 +191,12 @@ tp_status prepare_guide(const tp_dims* dims, const tp_batch* batch, const void* 
   for (int b = 0; b < batch->batch; ++b) {
     const int64_t nb = batch->ctx_offsets[b + 1] - batch->ctx_offsets[b];
     const int64_t gb = batch->guide_offsets[b + 1] - batch->guide_offsets[b];
-    const int64_t units = (int64_t)a.L * a.Hkv * ((nb + a.chunk - 1) / a.chunk);
+    const int64_t units = (int64_t)a.L * a.Hkv * tp::chunks_of(nb, a.chunk);
     wg += (units + 7) / 8 * 8 * ((a.R * gb + tp::kRowsPerGroup - 1) / tp::kRowsPerGroup);
     if (wg > 0x7FFFFFFF) return fail(TP_ERR_UNSUPPORTED, "context or guide too long for one launch");
     a.wg_off[b + 1] = (int32_t)wg;
   }
+  a.fold_lse = !guide_lse && wg <= tp::kFoldLseMaxWgs;
   return TP_OK;
 }
 
@@ -741,7 +742,7 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
   if (s != TP_OK) return s;
   // workspace: the score pass's, then (without s_out) the combined scores
   const size_t gws = guide_workspace_bytes(dims, batch);
-  const size_t ews = evict_workspace_bytes(dims, batch);
+  const size_t ews = gws + select_workspace(dims, batch);
   if (!workspace || ws_bytes < ews) return fail(TP_ERR_WORKSPACE, "workspace needs %zu bytes (got %zu)", ews, ws_bytes);
   tp::GuideArgs ga;
   s = prepare_guide(dims, batch, q_guide, k, k_guide, guide_lse, softmax_scale, pool_k, s_key, workspace, gws, ga);

@@ -6,7 +6,7 @@
 //   s_key_i = (1/K) sum_{|t|<=K/2} raw_{i+t}                           (zero-padded pooling)
 // The exact per-row normaliser lse_row needs every logit of the row, so the logits are
 // produced twice (never stored): pass 1 keeps an online (max, sum) per row and chunk,
-// a small kernel merges the chunks into lse, and pass 2 recomputes the logits and sums the
+// a small kernel (or, in small calls, pass 2) merges the chunks into lse, and pass 2 recomputes the logits and sums the
 // normalised weights per token.  Everything is kept in the log2 domain:
 // x' = x * scale * log2(e), exp2(x' - lse2).
 //
@@ -16,23 +16,29 @@
 // token's sum over rows reduces inside the lane).  The same register fragments serve both
 // orientations because the A and B operand layouts of the instruction coincide.
 //
-// A workgroup (8 waves, one per CU) takes one chunk of 8192 tokens and one group of <= 256
-// guide rows.  The group's queries sit in LDS for the whole chunk.  Each wave streams its
+// A workgroup (8 waves, one per CU) takes one chunk of 256 to 16384 tokens (plan_chunk) and one
+// group of <= 256 guide rows.  The group's queries sit in LDS for the whole chunk.  Each wave streams its
 // own 32-token K sub-tiles: an asynchronous global->LDS copy into the wave's private
 // staging buffer runs while the wave computes the previous sub-tile from registers, so no
 // barrier is needed inside the main loop and the K fragments take no prefetch registers.
 // Inside a sub-tile the wave is software-pipelined: the MFMAs of one pair of 32-row blocks
 // run while the vector ALU does the softmax work of the previous pair.
+#include <math.h>
+
 #include "tile_common.h"
 #include "tp_internal.h"
 
 namespace tp {
 namespace {
 
+constexpr double kCus = 256.0;      // score-pass workgroups in flight: one per CU
+constexpr uint32_t kLongContext = 65536;
+constexpr double kWgTokens = 350.0; // a workgroup's fixed work (5 us: query staging, merge) in tokens of a 256-row chunk
+
 struct Work {
   int b, seg, l, h, rg, chunk;
   int64_t n0, nb, c0, c1, g0;
-  int gb, rows, row0, nrows;
+  int gb, rows, row0, nrows, nchunk;
 };
 
 
@@ -53,7 +59,9 @@ __device__ inline bool decode(const GuideArgs& a, Work& w) {
   w.gb = (int)(a.bt.g_off[b + 1] - w.g0);
   w.rows = a.R * w.gb;
   const int nrg = (w.rows + kRowsPerGroup - 1) / kRowsPerGroup;
-  const int nchunk = (int)((w.nb + a.chunk - 1) / a.chunk);
+  const int csize = balanced_chunk(w.nb, a.chunk);
+  const int nchunk = (int)(((uint32_t)w.nb + (uint32_t)csize - 1u) / (uint32_t)csize);
+  w.nchunk = nchunk;
   const int xcd = xb & 7, slot = xb >> 3;
   w.rg = slot % nrg;
   const int64_t unit = (int64_t)(slot / nrg) * 8 + xcd;
@@ -62,8 +70,8 @@ __device__ inline bool decode(const GuideArgs& a, Work& w) {
   w.chunk = (int)(unit % nchunk);
   w.l = w.seg / a.Hkv;
   w.h = w.seg % a.Hkv;
-  w.c0 = (int64_t)w.chunk * a.chunk;
-  w.c1 = w.c0 + a.chunk < w.nb ? w.c0 + a.chunk : w.nb;
+  w.c0 = (int64_t)w.chunk * csize;
+  w.c1 = w.c0 + csize < w.nb ? w.c0 + csize : w.nb;
   w.row0 = w.rg * kRowsPerGroup;
   w.nrows = w.rows - w.row0 < kRowsPerGroup ? w.rows - w.row0 : kRowsPerGroup;
   return true;
@@ -80,14 +88,25 @@ __device__ inline int64_t grow_of(const GuideArgs& a, const Work& w, int rho) {
 // per row makes 16 consecutive rows start on different bank groups, so the fragment reads
 // below are conflict-free, and every fragment address is one per-lane base plus a constant.
 // Rows past the group's end repeat its last row (finite data, discarded later).
-template <int D>
-__device__ inline void stage_q(const GuideArgs& a, const Work& w, char* qs, int nrows_pad) {
+// All of a thread's loads are issued before the first is written to LDS: one memory latency per
+// workgroup instead of one per 32 rows.
+template <int D, int NB>
+__device__ inline void stage_q(const GuideArgs& a, const Work& w, char* qs) {
   using C = Cfg<D>;
-  for (int t = threadIdx.x; t < nrows_pad * C::kPieces; t += kGuideThreads) {
-    const int rr = t / C::kPieces, p = t % C::kPieces;
+  constexpr int kRows = kGuideThreads / C::kPieces;  // rows per sweep of the workgroup
+  constexpr int kSweeps = (NB * 32 + kRows - 1) / kRows;
+  const int rr0 = threadIdx.x / C::kPieces, p = threadIdx.x % C::kPieces;
+  uint4 v[kSweeps];
+#pragma unroll
+  for (int i = 0; i < kSweeps; ++i) {
+    const int rr = rr0 + i * kRows;
     const int src_row = rr < w.nrows ? rr : w.nrows - 1;
-    const uint4 v = *(const uint4*)(a.q + grow_of(a, w, w.row0 + src_row) * D + p * 8);
-    *(uint4*)(qs + rr * C::kStride + p * 16) = v;
+    v[i] = *(const uint4*)(a.q + grow_of(a, w, w.row0 + src_row) * D + p * 8);
+  }
+#pragma unroll
+  for (int i = 0; i < kSweeps; ++i) {
+    const int rr = rr0 + i * kRows;
+    if (NB * 32 % kRows == 0 || rr < NB * 32) *(uint4*)(qs + rr * C::kStride + p * 16) = v[i];
   }
 }
 
@@ -299,7 +318,7 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_stats(GuideArgs a) {
   const int nfull = ntok / 32;
   int st = wave;
   if (st < nfull) dma_subtile<D>(kchunk, 32 * st, ntok, kbuf);
-  stage_q<D>(a, w, qs, NB * 32);
+  stage_q<D, NB>(a, w, qs);
   __syncthreads();
 
   float sm[NB], ss[NB];
@@ -431,7 +450,7 @@ __global__ __launch_bounds__(256) void k_guide_lse(GuideArgs a) {
   const int64_t qh = rem / gb, j = rem - qh * gb;
   const int64_t grow = (l * a.Hq + qh) * a.g_tot + g0 + j;
   const int64_t growtot = (int64_t)a.L * a.Hq * a.g_tot;
-  const int nch = (int)((nb + a.chunk - 1) / a.chunk);
+  const int nch = chunks_of(nb, a.chunk);
   float m = kNoMax, s = 0.f;
   for (int c = 0; c < nch; ++c) {
     const float2 v = a.stats[(int64_t)c * growtot + grow];
@@ -469,6 +488,47 @@ __device__ inline void read_lz(const float* lz_s, int rb, f32x16& acc) {
     acc[4 * g + 1] = v.y;
     acc[4 * g + 2] = v.z;
     acc[4 * g + 3] = v.w;
+  }
+}
+
+// The row group's accumulator start values -lse2/c in LDS, from whichever form the row
+// normalisers are in: the caller's natural logs, the merged lse2, or (fold_lse) the chunks'
+// statistics, which P adjacent lanes per row merge here.  Every workgroup of a row merges in
+// the same order, so all use the same value.
+template <int NB>
+__device__ inline void stage_lz(const GuideArgs& a, const Work& w, float* lz_s) {
+  if (a.fold_lse) {
+    constexpr int P = NB * 32 <= 64 ? 8 : (NB * 32 <= 128 ? 4 : 2);
+    static_assert(NB * 32 * P <= kGuideThreads, "a row's lanes fit one sweep of the workgroup");
+    const int t = threadIdx.x / P, part = threadIdx.x % P;
+    const int64_t growtot = (int64_t)a.L * a.Hq * a.g_tot;
+    const bool live = t < w.nrows;
+    const float2* st = a.stats + (live ? grow_of(a, w, w.row0 + t) : 0);
+    float m = kNoMax, s = 0.f;
+    if (live) {
+#pragma unroll 4
+      for (int c = part; c < w.nchunk; c += P) {
+        const float2 v = st[(int64_t)c * growtot];
+        merge_stats(m, s, v.x, v.y);
+      }
+      if (part == 0 && a.kg != nullptr) {
+        const float2 v = st[(int64_t)a.nchunk_max * growtot];
+        merge_stats(m, s, v.x, v.y);
+      }
+    }
+#pragma unroll
+    for (int o = 1; o < P; o <<= 1) merge_stats(m, s, __shfl_xor(m, o), __shfl_xor(s, o));
+    if (part == 0 && t < NB * 32) lz_s[t] = live ? -(m + log2f(s)) / a.c : -INFINITY;
+    return;
+  }
+  for (int t = threadIdx.x; t < NB * 32; t += kGuideThreads) {  // padding rows: exp2(-inf) = 0
+    float z = -INFINITY;
+    if (t < w.nrows) {
+      const int64_t grow = grow_of(a, w, w.row0 + t);
+      const float lse2 = a.lse_in ? (float)((double)a.lse_in[grow] * 1.4426950408889634) : a.lse2[grow];
+      z = -lse2 / a.c;
+    }
+    lz_s[t] = z;
   }
 }
 
@@ -528,9 +588,8 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_attn(GuideArgs a) {
   const int nsub = (ntok + 31) / 32;
   int st = wave;
   if (st < nsub) dma_subtile<D>(kchunk, 32 * st, ntok, kbuf);
-  stage_q<D>(a, w, qs, NB * 32);
-  for (int t = threadIdx.x; t < NB * 32; t += kGuideThreads)  // padding rows: exp2(-inf) = 0
-    lz_s[t] = t < w.nrows ? -a.lse2[grow_of(a, w, w.row0 + t)] / a.c : -INFINITY;
+  stage_q<D, NB>(a, w, qs);
+  stage_lz<NB>(a, w, lz_s);
   __syncthreads();
 
   float* raw_out = a.raw + ((int64_t)w.rg * a.L * a.Hkv + w.seg) * a.n_tot + w.n0 + w.c0;
@@ -623,12 +682,6 @@ __global__ __launch_bounds__(256) void k_guide_pool(GuideArgs a) {
   }
 }
 
-// Row normalisers supplied by the caller (natural log) -> the log2 domain of pass 2.
-__global__ __launch_bounds__(256) void k_lse_import(const float* lse, float* lse2, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) lse2[i] = (float)((double)lse[i] * 1.4426950408889634);
-}
-
 template <int D, int NP>
 hipError_t launch_pass(const GuideArgs& a, bool attn, hipStream_t stream) {
   const unsigned nwg = (unsigned)a.wg_off[a.bt.batch];
@@ -646,7 +699,7 @@ hipError_t launch_pass(const GuideArgs& a, bool attn, hipStream_t stream) {
 // arguments give the other sequences empty workgroup ranges.
 template <int D>
 hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, GuideBetween between, void* ctx) {
-  static_assert(kChunkSmall % (32 * kGuideWaves) == 0, "every wave owns whole sub-tiles of a chunk");
+  static_assert(kChunkUnit % (32 * kGuideWaves) == 0, "every wave owns whole sub-tiles of a chunk");
   int64_t max_nb = 0, max_gb = 0;
   // per pass and class NP (1..4 staged row-block pairs) the launch arguments, with the other
   // classes' sequences given empty workgroup ranges.  Pass 1 has no NP = 3 class: its
@@ -667,7 +720,7 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
     if (gb > max_gb) max_gb = gb;
     const int64_t rows = (int64_t)a.R * gb;
     const int np = (int)(((rows < kRowsPerGroup ? rows : kRowsPerGroup) + 63) / 64);
-    const int64_t units = (int64_t)a.L * a.Hkv * ((nb + a.chunk - 1) / a.chunk);
+    const int64_t units = (int64_t)a.L * a.Hkv * chunks_of(nb, a.chunk);
     const int64_t seq_wg = (units + 7) / 8 * 8 * ((rows + kRowsPerGroup - 1) / kRowsPerGroup);
     wg[0][np == 3 ? 3 : np - 1] += seq_wg;
     wg[1][np - 1] += seq_wg;
@@ -677,10 +730,6 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
   for (int pass = 0; pass < 2; ++pass) {  // the large classes first: shorter tail
     if (pass == 0 && a.lse_in) {  // normalisers given: no pass 1
       hipError_t e = ev ? hipEventRecord(ev[0], stream) : hipSuccess;
-      if (e != hipSuccess) return e;
-      const int64_t n = (int64_t)a.L * a.Hq * a.g_tot;
-      hipLaunchKernelGGL(k_lse_import, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a.lse_in, a.lse2, n);
-      e = hipGetLastError();
       if (e == hipSuccess && ev) e = hipEventRecord(ev[1], stream);
       if (e == hipSuccess && between) e = between(ctx);
       if (e != hipSuccess) return e;
@@ -697,8 +746,10 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
         const dim3 kgrid((unsigned)((a.R * max_gb + 255) / 256), (unsigned)(a.L * a.Hkv), (unsigned)a.bt.batch);
         hipLaunchKernelGGL(k_guide_key_stats<D>, kgrid, dim3(256), 0, stream, a);
       }
-      const dim3 lgrid((unsigned)((a.L * a.Hq * max_gb + 255) / 256), (unsigned)a.bt.batch);
-      hipLaunchKernelGGL(k_guide_lse<D>, lgrid, dim3(256), 0, stream, a);
+      if (!a.fold_lse) {
+        const dim3 lgrid((unsigned)((a.L * a.Hq * max_gb + 255) / 256), (unsigned)a.bt.batch);
+        hipLaunchKernelGGL(k_guide_lse<D>, lgrid, dim3(256), 0, stream, a);
+      }
       e = hipGetLastError();
       if (e == hipSuccess && ev) e = hipEventRecord(ev[1], stream);
       if (e == hipSuccess && between) e = between(ctx);
@@ -715,6 +766,68 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
 
 }  // namespace
 
+// The call's target chunk: the candidate with the least estimated pass time, sum over the
+// launches (row-block classes) of rounds of workgroups over the CUs x (a workgroup's fixed work
+// + its tokens).  Many rounds favour long chunks (less fixed work per token), few rounds
+// chunks short enough to occupy every CU.  Both passes together (no quantisation beside them),
+// us at 8192-token chunks and at the target chosen: one layer of 32q/8kv heads with 64 guide
+// tokens at 32768 tokens 200 -> 61 (1024), three layers at 131072 tokens 524 -> 499 (4096),
+// 24 layers at 9000 tokens 309 -> 295 (one chunk per segment).  The usual target is 16384 when
+// every sequence has 65536 tokens or more, else 8192 (32 layers at 32768 tokens, the whole
+// tp_evict: 1844 us at 8192, 1880 at 16384, whose last round ends later); a candidate has to be
+// estimated 3 % better.
+int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off, int32_t batch) {
+  static const int32_t kTargets[] = {16384, 14336, 12288, 10240, 8192, 7168, 6144, 5120, 4096, 3584, 3072,
+                                     2560,  2048,  1792,  1536,  1280, 1024, 768,  512,  256};
+  static const double kTokenCost[4] = {0.75, 0.75, 0.8, 1.0};  // by staged row-block pairs: K's bytes bound few rows
+  const int64_t R = Hq / Hkv, segs = (int64_t)L * Hkv;
+  struct Seq {
+    uint32_t n;  // context tokens
+    int cls;     // row-block class
+    double rg;   // row groups
+  } seq[TP_MAX_BATCH];
+  for (int b = 0; b < batch; ++b) {
+    const int64_t rows = R * (g_off[b + 1] - g_off[b]);
+    seq[b].n = (uint32_t)(ctx_off[b + 1] - ctx_off[b]);
+    seq[b].cls = (int)(((rows < kRowsPerGroup ? rows : kRowsPerGroup) + 63) / 64) - 1;
+    seq[b].rg = (double)((rows + kRowsPerGroup - 1) / kRowsPerGroup);
+  }
+  bool all_long = true;
+  for (int b = 0; b < batch; ++b) all_long = all_long && seq[b].n >= kLongContext;
+  const int32_t usual = all_long ? 16384 : 8192;
+  struct Cost {
+    double time, rounds;
+  };
+  auto cost_of = [&](int32_t target) {
+    double wgs[4] = {0, 0, 0, 0};
+    uint32_t longest[4] = {0, 0, 0, 0};
+    for (int b = 0; b < batch; ++b) {
+      const uint32_t c = (uint32_t)balanced_chunk(seq[b].n, target);
+      wgs[seq[b].cls] += (double)((segs * ((seq[b].n + c - 1u) / c) + 7) / 8 * 8) * seq[b].rg;
+      if (c > longest[seq[b].cls]) longest[seq[b].cls] = c;
+    }
+    Cost cost{0.0, 0.0};
+    for (int i = 0; i < 4; ++i) {
+      if (wgs[i] <= 0) continue;
+      const double r = ceil(wgs[i] / kCus);
+      cost.rounds += r;
+      cost.time += r * (kWgTokens + kTokenCost[i] * longest[i]);
+    }
+    return cost;
+  };
+  int32_t best = usual;
+  double least = cost_of(usual).time * 0.97;
+  for (const int32_t target : kTargets) {
+    const Cost c = cost_of(target);
+    if (c.time < least) {
+      best = target;
+      least = c.time;
+    }
+    if (c.rounds >= 64.0) break;  // shorter chunks only add fixed work from here on
+  }
+  return best;
+}
+
 GuideWorkspace guide_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off,
                                       const int64_t* g_off, int32_t batch) {
   int64_t max_nb = 0, max_gb = 0;
@@ -724,11 +837,12 @@ GuideWorkspace guide_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, const 
   }
   const int64_t n_tot = ctx_off[batch], g_tot = g_off[batch];
   const int64_t R = Hq / Hkv;
-  const int64_t chunk = chunk_tokens(ctx_off, batch);
+  const int32_t chunk = plan_chunk(L, Hq, Hkv, ctx_off, g_off, batch);
   const int64_t nchunk = (max_nb + chunk - 1) / chunk;
   const int64_t nrg = (R * max_gb + kRowsPerGroup - 1) / kRowsPerGroup;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   GuideWorkspace w;
+  w.chunk = chunk;
   w.stats_off = 0;  // nchunk slots of per-chunk statistics, plus one for the guide keys
   w.lse_off = up((size_t)(nchunk + 1) * L * Hq * g_tot * sizeof(float2));
   w.raw_off = w.lse_off + up((size_t)L * Hq * g_tot * sizeof(float));

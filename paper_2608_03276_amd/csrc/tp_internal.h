@@ -21,18 +21,31 @@ struct BatchArgs {
 constexpr int kGuideThreads = 512;       // 8 waves of 64, two per SIMD
 constexpr int kGuideWaves = kGuideThreads / 64;
 constexpr int kRowsPerGroup = 256;       // guide rows handled by one workgroup
-// Context tokens of one segment per score-pass workgroup (a "chunk"): 16384 when every
-// sequence of the batch has at least 65536 context tokens, so the per-workgroup query
-// staging and statistics merge are spread over more tokens; else 8192, so short and ragged
-// sequences keep enough workgroups and little padding.
-constexpr int kChunkSmall = 8192;
-constexpr int kChunkLarge = 16384;
-constexpr int64_t kLongContext = 65536;
-inline int32_t chunk_tokens(const int64_t* ctx_off, int32_t batch) {
-  for (int b = 0; b < batch; ++b)
-    if (ctx_off[b + 1] - ctx_off[b] < kLongContext) return kChunkSmall;
-  return kChunkLarge;
+// Context tokens of one segment per score-pass workgroup (a "chunk"): a call's target is at
+// most 16384 (long chunks spread the query staging and the statistics merge over more tokens)
+// and shorter where those would leave the chip idle or its last round of workgroups nearly
+// empty.  Always a multiple of 256, so every wave of a workgroup gets the same number of
+// 32-token sub-tiles.
+constexpr int kChunkUnit = 256;
+int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off, int32_t batch);
+
+// Chunk of one sequence of n tokens under the call's `target`: the sequence is cut into
+// ceil(n / target) equal parts, rounded up to kChunkUnit (so never above the target), instead
+// of full chunks and a remainder whose workgroups end early.  n <= 2^30.
+__host__ __device__ inline int32_t balanced_chunk(int64_t n, int32_t target) {
+  const uint32_t parts = ((uint32_t)n + (uint32_t)target - 1u) / (uint32_t)target;
+  const uint32_t per = ((uint32_t)n + parts - 1u) / parts;
+  return (int32_t)((per + kChunkUnit - 1u) & ~(uint32_t)(kChunkUnit - 1));
 }
+// Chunks of a sequence of n tokens (never more than ceil(n / target)).
+__host__ __device__ inline int32_t chunks_of(int64_t n, int32_t target) {
+  const uint32_t c = (uint32_t)balanced_chunk(n, target);
+  return (int32_t)(((uint32_t)n + c - 1u) / c);
+}
+
+// Pass 2 merges the chunks' statistics itself up to this many workgroups (three rounds of the
+// chip); a separate launch costs about 6 us, the merge inside about 2 us a round.
+constexpr int64_t kFoldLseMaxWgs = 768;
 
 struct GuideArgs {
   const uint16_t* q;  // bf16 [L][Hq][G_tot][d]
@@ -49,19 +62,22 @@ struct GuideArgs {
   float c;            // softmax_scale * log2(e)
   float pool_inv;     // 1 / (R * pool_k)
   int32_t pool_half;  // pool_k / 2
-  int32_t chunk;      // context tokens per chunk (chunk_tokens of the batch)
-  int32_t nchunk_max; // chunks of the longest sequence
+  int32_t chunk;      // target context tokens per chunk (plan_chunk of the call)
+  int32_t nchunk_max; // statistics slots of the context chunks: ceil(longest sequence / chunk)
   int32_t nrg_max;    // row groups of the largest R * G_b
   BatchArgs bt;
   // first workgroup of each sequence's range in the score passes: sequence b has
   // ceil(L * Hkv * nchunk_b / 8) * 8 * nrg_b workgroups
   int32_t wg_off[TP_MAX_BATCH + 1];
-  // the pooling kernel is left out (the split selection pools the raw sums itself)
+  // the pooling kernel is left out (the selection pools the raw sums itself)
   int32_t skip_pool;
+  // pass 2 merges the chunks' statistics itself (few workgroups: cheaper than a launch)
+  int32_t fold_lse;
 };
 
 struct GuideWorkspace {
   size_t stats_off, lse_off, raw_off, total;
+  int32_t chunk;  // plan_chunk of the call, which the layout follows
 };
 GuideWorkspace guide_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off,
                                       const int64_t* g_off, int32_t batch);
