@@ -21,8 +21,8 @@
  *    `stream` is a hipStream_t (NULL = the default stream).
  *  - Ownership: the caller allocates every input, output and workspace buffer.
  *    The library allocates no memory and keeps no pointer after returning; buffers
- *    must stay valid until the enqueued work has completed.  (tp_evict keeps one
- *    stream and four events of its own per device: see tp_evict.)
+ *    must stay valid until the enqueued work has completed.  (Large tp_evict calls keep
+ *    one stream and four events of the library's per device: see tp_evict.)
  *  - Execution is asynchronous and stream-ordered; nothing synchronises inside a
  *    call.  Calls are re-entrant.  Results are bit-identical from run to run (no
  *    floating-point atomics; fixed reduction orders).
@@ -301,7 +301,8 @@ tp_status tp_compact_quantize_kv(const tp_dims* dims, const tp_batch* batch, con
  * [6] after the selection, [7] after the compaction; one kernel runs between consecutive
  * events, except that a step which needs no kernel has none: with guide_lse, none from [0] to
  * [2]; in small calls, where score pass 2 merges the row normalisers itself, none between [1]
- * and [2].
+ * and [2]; where one kernel pools and selects (contexts of up to 65536 tokens), none between
+ * [5] and [6].
  * num_events = 0 (or a NULL profile) records none.
  */
 #define TP_EVICT_EVENTS 8
@@ -326,15 +327,16 @@ typedef struct tp_profile {
  * TP_ERR_NULL), and everything runs on `stream` (no second stream, no library state).
  * workspace: >= tp_workspace_size(TP_FN_EVICT, ...) bytes, 256-byte aligned (the score
  * pass's workspace followed by the selection's).
- * Step 2 of most V rows runs on a second stream of the library's: 2/5 concurrently with each
- * score pass (half with each when v_q is NULL), or, with guide_lse given, the first half
- * (3/5 when v_q is NULL) concurrently with the rest of the step; the arithmetic is the same,
- * so the results are as for the separate calls.  That stream and four events are created, with default priority, by the first
- * tp_evict call on a device and kept until the process ends (TP_ERR_HIP if that fails); the
- * work is forked from and joined back to `stream`, so the call stays stream-ordered and may
- * be captured into a graph (once the first call on the device, which creates the stream,
- * has been made outside capture).  Calls on one device enqueue one at a time (a lock held while
- * enqueueing, not while the work runs).
+ * In large calls (V of 640 MB or more; 1 GB with guide_lse) step 2 of most V rows runs on a
+ * second stream of the library's: 2/5 concurrently with each score pass (half with each when
+ * v_q is NULL), or, with guide_lse given, the last half (3/5 when v_q is NULL) concurrently
+ * with score pass 2; smaller calls run everything on `stream`.  The arithmetic is the same, so
+ * the results are as for the separate calls.  That stream and four events are created, with
+ * default priority, by the first such call on a device and kept until the process ends
+ * (TP_ERR_HIP if that fails); the work is forked from and joined back to `stream`, so the call
+ * stays stream-ordered and may be captured into a graph (once the first large call on the
+ * device, which creates the stream, has been made outside capture).  Large calls on one device
+ * enqueue one at a time (a lock held while enqueueing, not while the work runs).
  * Every argument is validated before anything is enqueued.  Errors as for the four calls.
  */
 tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_guide, const void* k,

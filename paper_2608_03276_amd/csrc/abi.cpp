@@ -367,8 +367,8 @@ size_t evict_workspace_bytes(const tp_dims* dims, const tp_batch* batch) {
 }
 
 // The second stream of tp_evict on one device and the events that fork it from, and join it
-// to, the caller's stream (part1: the first part of step 2 on it is done): created by the first tp_evict call on that device and kept until
-// the process ends.  `enqueue` is held while a call enqueues its work, so calls from several
+// to, the caller's stream (part1: the first part of step 2 on it is done): created by the first
+// tp_evict call on that device that overlaps step 2 and kept until the process ends.  `enqueue` is held while a call enqueues its work, so calls from several
 // threads do not interleave their uses of the events.
 struct AuxStream {
   std::mutex enqueue;
@@ -697,24 +697,40 @@ tp_status tp_compact_quantize_kv(const tp_dims* dims, const tp_batch* batch, con
 
 }  // extern "C"
 
-// tp_evict when step 2 was done beforehand: steps 1, 3 and 4 on the caller's stream only.
-// Event [3] (after step 2) follows [2] with no kernel between them.
-static tp_status evict_without_step2(const tp::GuideArgs& ga, const tp::SelectArgs& sa, const tp::CompactArgs& ca,
-                                     bool fuse_pool, const tp_dims* dims, hipStream_t st, hipEvent_t* ev) {
-  struct Rec {
+// Whether tp_evict spreads step 2 over a second stream beside the score passes: only where the
+// quantisation it hides is longer than the forks and joins (and the split into three launches)
+// cost.  The lines, in bytes of V, with and without score pass 1 (us per call at 32768 tokens of
+// 32q/8kv heads, int8, second stream against one): with pass 1 64 MB 147 / 108, 512 MB 485 / 481,
+// 640 MB 590 / 590, 768 MB 693 / 722, 2 GB 1690 / 1840; normalisers given 512 MB 355 / 338, 1 GB
+// 627 / 628, 1.5 GB 915 / 946.
+static bool step2_overlaps(int64_t rows, int32_t head_dim, bool pass1) {
+  const int64_t line = pass1 ? (int64_t)640 << 20 : (int64_t)1024 << 20;
+  return rows * head_dim * 2 >= line;
+}
+
+// tp_evict on the caller's stream alone: with `qa`, step 2 between the row normalisers and score
+// pass 2 (which then follows a memory-bound kernel, at a higher clock); without, step 2 was done
+// beforehand, and event [3] (after step 2) follows [2] with no kernel between them.
+static tp_status evict_one_stream(const tp::GuideArgs& ga, const tp::QuantArgs* qa, const tp::SelectArgs& sa,
+                                  const tp::CompactArgs& ca, bool fuse_pool, const tp_dims* dims, hipStream_t st,
+                                  hipEvent_t* ev) {
+  struct Mid {
+    const tp::QuantArgs* qa;
+    int head_dim;
     hipEvent_t done;
     hipStream_t st;
-  } rec{ev ? ev[3] : nullptr, st};
+  } mid{qa, dims->head_dim, ev ? ev[3] : nullptr, st};
   auto mark = [](void* c) -> hipError_t {
-    const Rec* r = (const Rec*)c;
-    return r->done ? hipEventRecord(r->done, r->st) : hipSuccess;
+    const Mid* m = (const Mid*)c;
+    const hipError_t r = m->qa ? tp::launch_quantize(*m->qa, m->head_dim, m->st) : hipSuccess;
+    return r == hipSuccess && m->done ? hipEventRecord(m->done, m->st) : r;
   };
   const int segs = dims->num_layers * dims->num_kv_heads;
   hipEvent_t gev[4] = {ev ? ev[1] : nullptr, ev ? ev[2] : nullptr, ev ? ev[4] : nullptr,
                        ev && !fuse_pool ? ev[5] : nullptr};
   hipError_t e = hipSuccess;
   if (ev) e = hipEventRecord(ev[0], st);
-  if (e == hipSuccess) e = tp::launch_guide_scores(ga, dims->head_dim, st, ev ? gev : nullptr, mark, &rec);
+  if (e == hipSuccess) e = tp::launch_guide_scores(ga, dims->head_dim, st, ev ? gev : nullptr, mark, &mid);
   if (e == hipSuccess) e = tp::launch_select(sa, segs, st, ev && fuse_pool ? ev[5] : nullptr);
   if (e == hipSuccess && ev) e = hipEventRecord(ev[6], st);
   if (e == hipSuccess) e = tp::launch_compact(ca, segs, dims->head_dim, st);
@@ -785,27 +801,35 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
 
   const hipStream_t st = (hipStream_t)stream;
   hipEvent_t* ev = (profile && profile->num_events) ? (hipEvent_t*)profile->events : nullptr;
-  if (!step2) return evict_without_step2(ga, sa, ca, fuse_pool, dims, st, ev);
+  if (!step2) return evict_one_stream(ga, nullptr, sa, ca, fuse_pool, dims, st, ev);
+  if (!step2_overlaps(qa.rows, dims->head_dim, ga.lse_in == nullptr))
+    return evict_one_stream(ga, &qa, sa, ca, fuse_pool, dims, st, ev);
   AuxStream* aux = nullptr;
   s = aux_stream_for(st, aux);
   if (s != TP_OK) return s;
   std::lock_guard<std::mutex> lk(aux->enqueue);
 
-  // Step 2 is split by rows of V, each row quantised once, by one of three launches with the
+  // Step 2 is split by rows of V, each row quantised once, by up to three launches with the
   // same arithmetic.  The lean kernel, on the second stream, takes the first part while score
   // pass 1 runs (its workgroups leave one wave slot and 48 VGPRs per SIMD free, and it uses
   // HBM well below the copy rate) and the last part while pass 2 runs; the regular kernel
   // takes the middle part between the normalisers and pass 2, which then starts after a
   // memory-bound kernel instead of right after pass 1, at a higher power-limited clock.
   // With pass 1 each lean part is 2/5 of the rows (the middle fifth runs alone), or half
-  // when only the scales are written (lighter, so all of it fits beside the passes); with the
-  // normalisers given (no pass 1) the lean kernel takes the first half (3/5 for scales only)
-  // and nothing runs beside pass 2.  Parts are rounded down to 64 rows.
+  // when only the scales are written (lighter, so all of it fits beside the passes).  With the
+  // normalisers given there is no pass 1: the regular kernel takes the first half (2/5 for
+  // scales only) and the lean kernel the rest beside pass 2, in twice as many workgroups as there
+  // are CUs, the second of each starting as pass 2 leaves its CU: the lean part outlasts
+  // pass 2, and one workgroup per CU moves 3.4 TB/s only (32 layers, int8 at 131072 tokens 5454
+  // us with the lean part beside the regular one at the start, 5295 beside pass 2 in 256
+  // workgroups, 5181 in 512; scales only 4385, 4277, 4099; int4 at 65536 2394, 2411, 2266).
+  // With pass 1, 512 workgroups take a CU from pass 2's next one (6817 -> 7266 us).
+  // Parts are rounded down to 64 rows.
   const bool pass1 = ga.lse_in == nullptr;
   const bool codes = qa.vq != nullptr;
   const int64_t num = pass1 ? (codes ? 2 : 1) : (codes ? 1 : 3), den = pass1 ? (codes ? 5 : 2) : (codes ? 2 : 5);
   const int64_t r_lean = qa.rows * num / den / 64 * 64;
-  const int64_t r_mid_end = pass1 ? qa.rows - r_lean : qa.rows;
+  const int64_t r_first = pass1 ? r_lean : 0, r_mid_end = qa.rows - r_lean;
   const int64_t vrow = (int64_t)row_bytes_of(qfmt, bits, dims->head_dim);
   auto part = [&](int64_t r0, int64_t r1) {
     tp::QuantArgs p = qa;
@@ -815,13 +839,15 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
     if (p.vq) p.vq += r0 * vrow;
     return p;
   };
-  const tp::QuantArgs qa1 = part(0, r_lean), qa2 = part(r_lean, r_mid_end), qa3 = part(r_mid_end, qa.rows);
+  const tp::QuantArgs qa1 = part(0, r_first), qa2 = part(r_first, r_mid_end), qa3 = part(r_mid_end, qa.rows);
   hipError_t e = hipSuccess;
   if (ev) e = hipEventRecord(ev[0], st);
-  if (e == hipSuccess) e = hipEventRecord(aux->fork, st);
-  if (e == hipSuccess) e = hipStreamWaitEvent(aux->stream, aux->fork, 0);
-  if (e == hipSuccess) e = tp::launch_quantize_lean(qa1, dims->head_dim, aux->stream);
-  if (e == hipSuccess) e = hipEventRecord(aux->part1, aux->stream);  // the first part's scales are written
+  if (pass1) {
+    if (e == hipSuccess) e = hipEventRecord(aux->fork, st);
+    if (e == hipSuccess) e = hipStreamWaitEvent(aux->stream, aux->fork, 0);
+    if (e == hipSuccess) e = tp::launch_quantize_lean(qa1, dims->head_dim, tp::kLeanBlocks, aux->stream);
+    if (e == hipSuccess) e = hipEventRecord(aux->part1, aux->stream);  // the first part's scales are written
+  }
   // called by the score pass between the normalisers and pass 2 (exactly once on success)
   struct Mid {
     const tp::QuantArgs* mid;
@@ -830,7 +856,8 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
     hipStream_t st;
     hipEvent_t done;
     AuxStream* aux;
-  } mid{&qa2, &qa3, dims->head_dim, st, ev ? ev[3] : nullptr, aux};
+    unsigned lean_blocks;
+  } mid{&qa2, &qa3, dims->head_dim, st, ev ? ev[3] : nullptr, aux, pass1 ? tp::kLeanBlocks : 2 * tp::kLeanBlocks};
   auto quant_between = [](void* c) -> hipError_t {
     const Mid* m = (const Mid*)c;
     hipError_t r = tp::launch_quantize(*m->mid, m->head_dim, m->st);
@@ -838,7 +865,7 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
     if (r == hipSuccess && m->last->rows > 0) {
       r = hipEventRecord(m->aux->fork2, m->st);
       if (r == hipSuccess) r = hipStreamWaitEvent(m->aux->stream, m->aux->fork2, 0);
-      if (r == hipSuccess) r = tp::launch_quantize_lean(*m->last, m->head_dim, m->aux->stream);
+      if (r == hipSuccess) r = tp::launch_quantize_lean(*m->last, m->head_dim, m->lean_blocks, m->aux->stream);
     }
     if (r == hipSuccess) r = hipEventRecord(m->aux->join, m->aux->stream);
     return r;
@@ -848,23 +875,14 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
   if (e == hipSuccess)
     e = tp::launch_guide_scores(ga, dims->head_dim, st, ev ? gev : nullptr, quant_between, &mid);
   // The selection reads the scales.  Segments whose V rows all belong to parts of step 2
-  // already done in this stream's order form their combined scores while the second stream
-  // finishes its last part; the rest wait for it.  With pass 1 those are the rows before the
-  // part beside pass 2 (the first part, on the second stream, is waited for by its own
-  // event); with the normalisers given, the rows after the second stream's part.
+  // already done in this stream's order, the rows before the part beside pass 2, form their
+  // combined scores while the second stream finishes that part (the first part, also on the
+  // second stream, is waited for by its own event); the rest wait for it.
   const int segs = dims->num_layers * dims->num_kv_heads;
   const int64_t n_tot = batch->ctx_offsets[batch->batch];
-  int rb = 0, re = 0;  // segments [rb, re) scored before the join
-  if (fuse_pool) {
-    if (pass1) {
-      re = (int)std::min<int64_t>(segs, r_mid_end / n_tot);
-    } else {
-      rb = (int)std::min<int64_t>(segs, (r_lean + n_tot - 1) / n_tot);
-      re = segs;
-    }
-  }
-  if (e == hipSuccess && re > rb && pass1) e = hipStreamWaitEvent(st, aux->part1, 0);
-  if (e == hipSuccess) e = tp::launch_select_score(sa, rb, re, segs, st);
+  const int re = fuse_pool ? (int)std::min<int64_t>(segs, r_mid_end / n_tot) : 0;  // segments [0, re) before the join
+  if (e == hipSuccess && re > 0 && pass1) e = hipStreamWaitEvent(st, aux->part1, 0);
+  if (e == hipSuccess) e = tp::launch_select_score(sa, 0, re, segs, st);
   if (e != hipSuccess) {
     // Work may already sit on the second stream (it was forked from `st` before the failure):
     // join it back, best effort, so nothing the caller's stream orders after this call can
@@ -873,7 +891,7 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
     return hip_fail(e, "tp_evict launch");
   }
   e = hipStreamWaitEvent(st, aux->join, 0);
-  if (e == hipSuccess) e = tp::launch_select(sa, segs, st, ev && fuse_pool ? ev[5] : nullptr, rb, re);
+  if (e == hipSuccess) e = tp::launch_select(sa, segs, st, ev && fuse_pool ? ev[5] : nullptr, re);
   if (e == hipSuccess && ev) e = hipEventRecord(ev[6], st);
   if (e == hipSuccess) e = tp::launch_compact(ca, dims->num_layers * dims->num_kv_heads, dims->head_dim, st);
   if (e == hipSuccess && ev) e = hipEventRecord(ev[7], st);

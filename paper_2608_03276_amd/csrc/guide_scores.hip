@@ -25,6 +25,8 @@
 // run while the vector ALU does the softmax work of the previous pair.
 #include <math.h>
 
+#include <algorithm>
+
 #include "tile_common.h"
 #include "tp_internal.h"
 
@@ -59,7 +61,7 @@ __device__ inline bool decode(const GuideArgs& a, Work& w) {
   w.gb = (int)(a.bt.g_off[b + 1] - w.g0);
   w.rows = a.R * w.gb;
   const int nrg = (w.rows + kRowsPerGroup - 1) / kRowsPerGroup;
-  const int csize = balanced_chunk(w.nb, a.chunk);
+  const int csize = seq_chunk(w.nb, a.chunk);
   const int nchunk = (int)(((uint32_t)w.nb + (uint32_t)csize - 1u) / (uint32_t)csize);
   w.nchunk = nchunk;
   const int xcd = xb & 7, slot = xb >> 3;
@@ -766,16 +768,15 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
 
 }  // namespace
 
-// The call's target chunk: the candidate with the least estimated pass time, sum over the
-// launches (row-block classes) of rounds of workgroups over the CUs x (a workgroup's fixed work
-// + its tokens).  Many rounds favour long chunks (less fixed work per token), few rounds
-// chunks short enough to occupy every CU.  Both passes together (no quantisation beside them),
-// us at 8192-token chunks and at the target chosen: one layer of 32q/8kv heads with 64 guide
-// tokens at 32768 tokens 200 -> 61 (1024), three layers at 131072 tokens 524 -> 499 (4096),
-// 24 layers at 9000 tokens 309 -> 295 (one chunk per segment).  The usual target is 16384 when
-// every sequence has 65536 tokens or more, else 8192 (32 layers at 32768 tokens, the whole
-// tp_evict: 1844 us at 8192, 1880 at 16384, whose last round ends later); a candidate has to be
-// estimated 3 % better.
+// The call's target chunk.  The usual one is 16384 when every sequence has 65536 tokens or more
+// (the query staging and the statistics merge are spread over more tokens), else 8192 (short
+// and ragged sequences; 32 layers at 32768 tokens, the whole tp_evict: 1844 us at 8192, 1880 at
+// 16384, whose last round ends later).  Calls that give it fewer than three rounds of workgroups
+// take the candidate with the least estimated pass time, the sum over the launches (row-block
+// classes) of rounds over the CUs x (a workgroup's fixed work + its tokens), where that is 3 %
+// less.  Both passes together, us at 8192 and at the target chosen: one layer of 32q/8kv heads
+// with 64 guide tokens at 32768 tokens 200 -> 64 (1024), four layers 208 -> 164 (4096), three
+// layers at 131072 tokens 524 -> 505 (4096), seven segments of 3924 tokens 108 -> 33 (256).
 int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off, int32_t batch) {
   static const int32_t kTargets[] = {16384, 14336, 12288, 10240, 8192, 7168, 6144, 5120, 4096, 3584, 3072,
                                      2560,  2048,  1792,  1536,  1280, 1024, 768,  512,  256};
@@ -802,28 +803,32 @@ int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, c
     double wgs[4] = {0, 0, 0, 0};
     uint32_t longest[4] = {0, 0, 0, 0};
     for (int b = 0; b < batch; ++b) {
-      const uint32_t c = (uint32_t)balanced_chunk(seq[b].n, target);
+      const uint32_t c = (uint32_t)seq_chunk(seq[b].n, target);
       wgs[seq[b].cls] += (double)((segs * ((seq[b].n + c - 1u) / c) + 7) / 8 * 8) * seq[b].rg;
-      if (c > longest[seq[b].cls]) longest[seq[b].cls] = c;
+      longest[seq[b].cls] = std::max(longest[seq[b].cls], std::min(c, seq[b].n));
     }
     Cost cost{0.0, 0.0};
     for (int i = 0; i < 4; ++i) {
       if (wgs[i] <= 0) continue;
-      const double r = ceil(wgs[i] / kCus);
+      // a partly filled last round costs half its length: its workgroups have the HBM and the
+      // power budget to themselves
+      const double whole = ceil(wgs[i] / kCus), r = whole > 1.0 ? 0.5 * (whole + wgs[i] / kCus) : 1.0;
       cost.rounds += r;
       cost.time += r * (kWgTokens + kTokenCost[i] * longest[i]);
     }
     return cost;
   };
+  const Cost at_usual = cost_of(usual);
+  if (at_usual.rounds >= 3.0) return usual;
   int32_t best = usual;
-  double least = cost_of(usual).time * 0.97;
+  double least = at_usual.time * 0.97;
   for (const int32_t target : kTargets) {
     const Cost c = cost_of(target);
     if (c.time < least) {
       best = target;
       least = c.time;
     }
-    if (c.rounds >= 64.0) break;  // shorter chunks only add fixed work from here on
+    if (c.rounds >= 16.0) break;  // shorter chunks only add fixed work from here on
   }
   return best;
 }

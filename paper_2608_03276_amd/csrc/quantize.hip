@@ -90,7 +90,6 @@ void launch_d(const QuantArgs& a, unsigned blocks, hipStream_t stream) {
 // compiler ignores a plain VGPR-count request), so the budget holds by construction (four
 // loads in flight: 42 VGPRs) and a build test checks that the two kernels fit together.
 constexpr int kLeanLoads = 4;
-constexpr int kLeanBlocks = 256;
 
 template <int D, int K>
 __global__ __launch_bounds__(kQuantThreads) void k_quantize_lean(QuantArgs a) {
@@ -137,8 +136,8 @@ __global__ __launch_bounds__(kQuantThreads) void k_quantize_lean(QuantArgs a) {
 }
 
 template <int D>
-void launch_lean_d(const QuantArgs& a, hipStream_t stream) {
-  const dim3 grid(kLeanBlocks), block(kQuantThreads);
+void launch_lean_d(const QuantArgs& a, unsigned blocks, hipStream_t stream) {
+  const dim3 grid(blocks), block(kQuantThreads);
   if (a.vq == nullptr) {
     hipLaunchKernelGGL((k_quantize_lean<D, kScalesOnly>), grid, block, 0, stream, a);
     return;
@@ -160,12 +159,12 @@ void launch_lean_d(const QuantArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_quantize_lean(const QuantArgs& a, int head_dim, hipStream_t stream) {
+hipError_t launch_quantize_lean(const QuantArgs& a, int head_dim, unsigned blocks, hipStream_t stream) {
   if (a.rows <= 0) return hipSuccess;
   if (head_dim == 128)
-    launch_lean_d<128>(a, stream);
+    launch_lean_d<128>(a, blocks, stream);
   else
-    launch_lean_d<64>(a, stream);
+    launch_lean_d<64>(a, blocks, stream);
   return hipGetLastError();
 }
 

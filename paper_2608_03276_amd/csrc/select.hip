@@ -2,19 +2,16 @@
 // aggregation table of Sec. 4.4) and the top-k kept set of every (sequence, layer, KV head)
 // (Sec. 3.4; uniform per-head budget, Sec. 4 setup).
 //
-// One 1024-thread workgroup per segment.  The combined score S is written once (fp32) and
-// ranked through the order-preserving map of its bit pattern to uint32:
-//   - a radix select finds the k-th largest key T and how many keys equal to T are needed
-//     (ties go to the lower index): a 12-bit histogram of the top digit while S is formed,
-//     then the keys in T's top-digit bucket are collected into LDS (when they fit; else the
-//     remaining digits re-read S from memory) and their 12-bit and 8-bit digits are ranked
-//     there, so S is read back only twice (collection and compaction) instead of once per
-//     digit;
-//   - an ordered compaction then emits, in ascending token order, every index with key > T
-//     plus the first `need` indices with key == T: its output slot is
-//     #(key > T before i) + min(#(key == T before i), need), from one block-wide scan of a
-//     packed (greater, equal) count per tile.
-// Only integer LDS atomics (histogram counts) are used, so the result is deterministic.
+// The combined score S is written once (fp32) and ranked through the order-preserving map of
+// its bit pattern to uint32: a radix select (12, 12 and 8 bits) finds the k-th largest key T and
+// how many keys equal to T are needed (ties go to the lower index); an ordered compaction then
+// emits, in ascending token order, every index with key > T plus the first `need` indices with
+// key == T: its output slot is #(key > T before i) + min(#(key == T before i), need).
+// Segments of up to 65536 tokens are selected by one workgroup each, whose registers hold
+// every key (k_sel_one: one launch); longer ones by several workgroups over five launches (the
+// split selection below).  Only integer LDS atomics (histogram counts) are used, so the result
+// is deterministic.
+#include <algorithm>
 #include <mutex>
 
 #include "tp_internal.h"
@@ -24,11 +21,9 @@ namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
-constexpr int kPerThread = 4;
-constexpr int kBatch = 16;  // keys each thread loads before it touches the histogram
+constexpr int kBatch = 16;  // keys each thread of k_sel_refine loads before it touches the histogram
 constexpr int kTopBits = 12;              // first digit: bits 31..20 of the key
 constexpr int kBins = 1 << kTopBits;      // histogram bins (the 8-bit last digit uses 256)
-constexpr int kCandCap = 16384;           // keys of the threshold's top-digit bucket held in LDS
 
 __device__ inline uint32_t order_key(float s) {
   uint32_t b = __float_as_uint(s);
@@ -36,6 +31,12 @@ __device__ inline uint32_t order_key(float s) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+// The reciprocal of a segment's L2 norm from its sum of squares (0 for an all-zero signal, whose
+// normalised values are 0).  One fp64 division per segment instead of two per token: the
+// product is within 1.5 units of 2^-53 of the quotient, before its one rounding to fp32.
+__device__ inline double inverse_norm(double sum_sq) { return sum_sq > 0.0 ? 1.0 / sqrt(sum_sq) : 0.0; }
+
+// na, nb: the inverse norms of s_key and the scales (TP_COMBINE_NORM_ADD only).
 __device__ inline float combine(int rule, float s, float g, double na, double nb) {
   switch (rule) {
     case TP_COMBINE_KEY_ONLY:
@@ -44,11 +45,8 @@ __device__ inline float combine(int rule, float s, float g, double na, double nb
       const double den = (double)s + (double)g;
       return den > 0.0 ? (float)((2.0 * (double)s * (double)g) / den) : 0.0f;
     }
-    case TP_COMBINE_NORM_ADD: {
-      const double ta = na > 0.0 ? (double)s / na : 0.0;
-      const double tb = nb > 0.0 ? (double)g / nb : 0.0;
-      return (float)(ta + tb);
-    }
+    case TP_COMBINE_NORM_ADD:
+      return (float)((double)s * na + (double)g * nb);
     default:
       return s * g;
   }
@@ -114,31 +112,134 @@ __device__ inline uint32_t block_scan(uint32_t v, uint32_t* sh, uint32_t& total)
   return r;
 }
 
-__global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
-  const int seg = blockIdx.x, b = blockIdx.y;
+// Lanes below this one in a wave's ballot mask.
+__device__ inline uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// ---------------------------------------------------------------------------- one workgroup per segment
+// k_sel_one keeps a segment's keys in registers, 4 G per thread, so S is formed, written, ranked
+// and emitted without being read back and without a second launch.  Bound by latency (a
+// dozen barriers and one sweep of loads) until every CU has a segment, then by the
+// sweep's bytes.  Thread t holds tokens 4 (g NT + t) - a0 .. + 3 of each group g (a0 = the
+// misalignment of the segment's first element), so every whole group is one aligned 16-byte
+// access whatever the segment's offset; the first and last groups go element by element.
+
+// Four consecutive floats p[t .. t+3] of a segment of n; elements outside [0, n) are 0.  vec: p + t
+// is 16-byte aligned.
+__device__ inline float4 load4(const float* p, int t, int n, bool vec) {
+  if (vec && t >= 0 && t + 3 < n) return *(const float4*)(p + t);
+  float4 v;
+  v.x = t >= 0 && t < n ? p[t] : 0.f;
+  v.y = t + 1 >= 0 && t + 1 < n ? p[t + 1] : 0.f;
+  v.z = t + 2 >= 0 && t + 2 < n ? p[t + 2] : 0.f;
+  v.w = t + 3 >= 0 && t + 3 < n ? p[t + 3] : 0.f;
+  return v;
+}
+
+__device__ inline void store4(float* p, int t, int n, const float (&v)[4]) {
+  if (t >= 0 && t + 3 < n) {
+    *(float4*)(p + t) = make_float4(v[0], v[1], v[2], v[3]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (t + j >= 0 && t + j < n) p[t + j] = v[j];
+  }
+}
+
+// The row groups' raw sums of four consecutive tokens, added in row-group order.
+__device__ inline float4 raw4(const float* raw, int nrg, int64_t stride, int t, int n) {
+  float4 v = load4(raw, t, n, true);
+  const bool vec = (stride & 3) == 0;
+  for (int rg = 1; rg < nrg; ++rg) {
+    const float4 u = load4(raw + rg * stride, t, n, vec);
+    v.x += u.x;
+    v.y += u.y;
+    v.z += u.z;
+    v.w += u.w;
+  }
+  return v;
+}
+
+// The value of the lane before (SHR) or after this one in the wave; `edge` at the wave's end.
+template <bool SHR>
+__device__ inline float lane_neighbour(float x, float edge) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(edge), (int)__float_as_uint(x),
+                                                               SHR ? 0x138 : 0x130, 0xF, 0xF, false));
+}
+
+// All threads: the digit of the krem-th largest key among the histogram's nbins (highest first)
+// and how many keys of that digit are still needed, into sel (read after the next barrier).
+template <int NT>
+__device__ inline void pick_digit_block(const uint32_t* hist, int nbins, uint32_t krem, uint32_t* sel, uint32_t* sh) {
+  const int per = nbins >= NT ? nbins / NT : 1;  // digits per thread, from the top
+  const int top = nbins - 1 - per * (int)threadIdx.x;
+  uint32_t sum = 0;
+  if (top >= 0)
+    for (int e = 0; e < per; ++e) sum += hist[top - e];
+  uint32_t total;
+  uint32_t cum = block_scan<NT / 64>(sum, sh, total);
+  if (top >= 0 && cum < krem && krem <= cum + sum) {
+    for (int e = 0; e < per; ++e) {
+      const uint32_t c = hist[top - e];
+      if (cum + c >= krem) {
+        sel[0] = (uint32_t)(top - e);
+        sel[1] = krem - cum;
+        break;
+      }
+      cum += c;
+    }
+  }
+}
+
+constexpr int kOneHalfMax = 4;      // widest pooling half-width k_sel_one takes (its window spans adjacent lanes)
+constexpr int kReadScore = -1;      // POOL: the key score is read, not pooled
+constexpr int kAnyHalf = -2;        // POOL: pooled, half-width a.pool_half <= kOneHalfMax; >= 0: that half-width
+
+template <int NT, int G, int POOL>
+__global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segments) {
+  constexpr int NW = NT / 64;
+  const int seg = seg0 + blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t n0 = a.bt.ctx_off[b];
-  const int64_t nb = a.bt.ctx_off[b + 1] - n0;
-  const int64_t k = a.k[b];
-  const float* sk = a.s_key + (int64_t)seg * a.n_tot + n0;
-  const float* sc = a.scales + (int64_t)seg * a.n_tot + n0;
-  float* sb = a.s_buf + (int64_t)seg * a.n_tot + n0;
-  int32_t* out = a.kept + (int64_t)seg * a.k_tot + a.kept_off[b];
+  const int n = (int)(a.bt.ctx_off[b + 1] - n0);
+  const uint32_t k = (uint32_t)a.k[b];
+  const int64_t base = (int64_t)seg * a.n_tot + n0;
+  const int a0 = (int)(base & 3);
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
+  __shared__ uint32_t scan_sh[NW + 1];
+  __shared__ double dred[NW][2];
+  __shared__ uint32_t sel[2];
+  __shared__ uint2 tab[G * NW];  // per group and wave: keys > T and == T, then those before it
+  const float* sc = a.scales + base;
+  const float* sk = POOL == kReadScore ? a.s_key + base : a.raw + base;
+  float* sb = a.s_buf + base;
+  // a fresh copy of the thread's id per use: the compiler then recomputes a group's token instead
+  // of keeping every group's tokens and addresses in registers beside the keys
+  auto tok_of = [&](int g) {
+    int t = tid;
+    if (G >= 8) asm volatile("" : "+v"(t));
+    return 4 * (g * NT + t) - a0;
+  };
 
-  __shared__ uint32_t hist[kBins];
-  __shared__ uint32_t cand[kCandCap];
-  __shared__ uint32_t scan_sh[kSelWaves + 1];
-  __shared__ double dred[kSelWaves][2];
-  __shared__ uint32_t sel[2];  // picked digit, keys of it still needed
-  __shared__ uint32_t ncand;
-
-  double norm_a = 0.0, norm_b = 0.0;
-  if (a.rule == TP_COMBINE_NORM_ADD) {
+  constexpr int GB = G < 4 ? G : 4;  // groups whose loads are in flight together
+  double norm_a = 0.0, norm_b = 0.0;  // inverse norms of the normalised-add rule
+  if (POOL == kReadScore && a.rule == TP_COMBINE_NORM_ADD) {
+    // the norms come first; the sweep below reads the same values again (from L2)
     double s1 = 0.0, s2 = 0.0;
-    for (int64_t i = tid; i < nb; i += kSelThreads) {
-      const double x = sk[i], y = sc[i];
-      s1 += x * x;
-      s2 += y * y;
+#pragma unroll 1
+    for (int g = 0; g < G; g += GB) {
+      float4 x[GB], y[GB];
+#pragma unroll
+      for (int e = 0; e < GB; ++e) {
+        x[e] = load4(sk, tok_of(g + e), n, true);
+        y[e] = load4(sc, tok_of(g + e), n, true);
+      }
+#pragma unroll
+      for (int e = 0; e < GB; ++e) {
+        s1 += (double)x[e].x * x[e].x + (double)x[e].y * x[e].y + (double)x[e].z * x[e].z + (double)x[e].w * x[e].w;
+        s2 += (double)y[e].x * y[e].x + (double)y[e].y * y[e].y + (double)y[e].z * y[e].z + (double)y[e].w * y[e].w;
+      }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -151,147 +252,181 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelectArgs a) {
     }
     __syncthreads();
     double t1 = 0.0, t2 = 0.0;
-    for (int w = 0; w < kSelWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
       t1 += dred[w][0];
       t2 += dred[w][1];
     }
-    norm_a = sqrt(t1);
-    norm_b = sqrt(t2);
+    norm_a = inverse_norm(t1);
+    norm_b = inverse_norm(t2);
   }
 
-  for (int i = tid; i < kBins; i += kSelThreads) hist[i] = 0;
+  for (int i = tid; i < kBins; i += NT) hist[i] = 0;
   __syncthreads();
-  // batches of kBatch keys per thread: the loads of a batch are in flight together
-  for (int64_t i0 = 0; i0 < nb; i0 += (int64_t)kSelThreads * kBatch) {
-    float x[kBatch], y[kBatch];
+  uint32_t key[4 * G];
 #pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int64_t i = i0 + (int64_t)e * kSelThreads + tid;
-      x[e] = i < nb ? sk[i] : 0.f;
-      y[e] = i < nb ? sc[i] : 0.f;
-    }
+  for (int gb = 0; gb < G; gb += GB) {
+    float4 x[GB], y[GB], edge[GB];
 #pragma unroll
-    for (int e = 0; e < kBatch; ++e) {
-      const int64_t i = i0 + (int64_t)e * kSelThreads + tid;
-      if (i < nb) {
-        const float S = combine(a.rule, x[e], y[e], norm_a, norm_b);
-        sb[i] = S;
-        atomicAdd(&hist[order_key(S) >> (32 - kTopBits)], 1u);
+    for (int e = 0; e < GB; ++e) {
+      const int t = tok_of(gb + e);
+      y[e] = load4(sc, t, n, true);
+      if (POOL == kReadScore) {
+        x[e] = load4(sk, t, n, true);
+      } else {
+        const int nrg = a.nrg[b];
+        const int64_t stride = (int64_t)segments * a.n_tot;
+        x[e] = raw4(sk, nrg, stride, t, n);
+        // the wave's ends take their outer neighbours from memory
+        edge[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (POOL != 0 && (lane == 0 || lane == 63)) edge[e] = raw4(sk, nrg, stride, lane == 0 ? t - 4 : t + 4, n);
       }
     }
+#pragma unroll
+    for (int e = 0; e < GB; ++e) {
+      const int t = tok_of(gb + e);
+      const float gam[4] = {y[e].x, y[e].y, y[e].z, y[e].w};
+      float s[4] = {x[e].x, x[e].y, x[e].z, x[e].w};
+      if (POOL != kReadScore) {
+        float w[12] = {lane_neighbour<true>(s[0], edge[e].x),
+                       lane_neighbour<true>(s[1], edge[e].y),
+                       lane_neighbour<true>(s[2], edge[e].z),
+                       lane_neighbour<true>(s[3], edge[e].w),
+                       s[0],
+                       s[1],
+                       s[2],
+                       s[3],
+                       lane_neighbour<false>(s[0], edge[e].x),
+                       lane_neighbour<false>(s[1], edge[e].y),
+                       lane_neighbour<false>(s[2], edge[e].z),
+                       lane_neighbour<false>(s[3], edge[e].w)};
+        // the window summed left to right from zero, as the pooling kernel does
+        const int half = POOL >= 0 ? POOL : a.pool_half;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float acc = 0.f;
+#pragma unroll
+          for (int d = -kOneHalfMax; d <= kOneHalfMax; ++d)
+            if (d <= half && -d <= half) acc += w[4 + j + d];
+          s[j] = acc * a.pool_inv;
+        }
+        store4(a.s_key_out + base, t, n, s);
+      }
+      float S[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        S[j] = combine(a.rule, s[j], gam[j], norm_a, norm_b);
+        // 0 marks a slot without a token; no key of a token is 0 (only a NaN's could be)
+        const uint32_t ky = t + j >= 0 && t + j < n ? max(order_key(S[j]), 1u) : 0u;
+        key[4 * (gb + e) + j] = ky;
+        if (ky != 0) atomicAdd(&hist[ky >> (32 - kTopBits)], 1u);
+      }
+      store4(sb, t, n, S);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // later groups' loads would spill the keys
   }
   __syncthreads();
-
-  if (wave == 0) pick_digit(hist, kBins, (uint32_t)k, sel);
+  pick_digit_block<NT>(hist, kBins, k, sel, scan_sh);
   __syncthreads();
   uint32_t prefix = sel[0], krem = sel[1];
-  const uint32_t bucket = hist[prefix];  // keys sharing T's top digit
-  const bool in_lds = bucket <= (uint32_t)kCandCap;
-  if (tid == 0) ncand = 0;
-  __syncthreads();
-  if (in_lds) {  // collect that bucket's keys (their order does not matter: only counts are used)
-    for (int64_t i0 = 0; i0 < nb; i0 += (int64_t)kSelThreads * kBatch) {
-      float x[kBatch];
-#pragma unroll
-      for (int e = 0; e < kBatch; ++e) {
-        const int64_t i = i0 + (int64_t)e * kSelThreads + tid;
-        x[e] = i < nb ? sb[i] : 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < kBatch; ++e) {
-        const int64_t i = i0 + (int64_t)e * kSelThreads + tid;
-        const uint32_t key = order_key(x[e]);
-        const bool hit = i < nb && (key >> (32 - kTopBits)) == prefix;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
-        if (m != 0) {  // one LDS atomic per wave
-          uint32_t base = 0;
-          if (lane == 0) base = atomicAdd(&ncand, (uint32_t)__builtin_popcountll(m));
-          base = __shfl(base, 0);
-          const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-          if (hit && base + rank < (uint32_t)kCandCap) cand[base + rank] = key;
-        }
-      }
-    }
-    __syncthreads();
-  }
   // the two remaining digits: bits 19..8 (12 bits), then bits 7..0 (8 bits)
+#pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
-    const int shift = pass == 0 ? 8 : 0;
-    const int nbins = pass == 0 ? kBins : 256;
-    const uint32_t mask = (uint32_t)nbins - 1u;
-    for (int i = tid; i < nbins; i += kSelThreads) hist[i] = 0;
+    const int shift = pass == 0 ? 8 : 0, bits = pass == 0 ? 12 : 8;
+    for (int i = tid; i < (1 << bits); i += NT) hist[i] = 0;
     __syncthreads();
-    if (in_lds) {
-      for (uint32_t i = tid; i < bucket; i += kSelThreads) {
-        const uint32_t key = cand[i];
-        if ((key >> (shift + (pass == 0 ? 12 : 8))) == prefix) atomicAdd(&hist[(key >> shift) & mask], 1u);
-      }
-    } else {
-      for (int64_t i0 = 0; i0 < nb; i0 += (int64_t)kSelThreads * kBatch) {
-        float x[kBatch];
 #pragma unroll
-        for (int e = 0; e < kBatch; ++e) {
-          const int64_t i = i0 + (int64_t)e * kSelThreads + tid;
-          x[e] = i < nb ? sb[i] : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < kBatch; ++e) {
-          const int64_t i = i0 + (int64_t)e * kSelThreads + tid;
-          const uint32_t key = order_key(x[e]);
-          if (i < nb && (key >> (shift + (pass == 0 ? 12 : 8))) == prefix) atomicAdd(&hist[(key >> shift) & mask], 1u);
-        }
-      }
+    for (int i = 0; i < 4 * G; ++i) {
+      if ((key[i] >> (shift + bits)) == prefix && key[i] != 0)
+        atomicAdd(&hist[(key[i] >> shift) & ((1u << bits) - 1u)], 1u);
     }
     __syncthreads();
-    if (wave == 0) pick_digit(hist, nbins, krem, sel);
+    pick_digit_block<NT>(hist, 1 << bits, krem, sel, scan_sh);
     __syncthreads();
-    prefix = (prefix << (pass == 0 ? 12 : 8)) | sel[0];
+    prefix = (prefix << bits) | sel[0];
     krem = sel[1];
-    __syncthreads();
   }
   const uint32_t T = prefix, need = krem;
-
-  uint32_t gt_run = 0, eq_run = 0;
-  for (int64_t t0 = 0; t0 < nb; t0 += (int64_t)kSelThreads * kPerThread) {
-    const int64_t i0 = t0 + (int64_t)tid * kPerThread;
-    uint32_t keys[kPerThread];
-    uint32_t gtc = 0, eqc = 0;
+  // keys > T and == T of each wave's 256 consecutive tokens per group, then their running sums
 #pragma unroll
-    for (int e = 0; e < kPerThread; ++e) {
-      const int64_t i = i0 + e;
-      keys[e] = i < nb ? order_key(sb[i]) : 0u;
-      if (i < nb) {
-        gtc += keys[e] > T;
-        eqc += keys[e] == T;
+  for (int g = 0; g < G; ++g) {
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      gt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[4 * g + j] > T));
+      eq += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[4 * g + j] == T));
+    }
+    if (lane == 0) tab[g * NW + wave] = make_uint2(gt, eq);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    constexpr int per = (G * NW + 63) / 64;
+    uint32_t gs = 0, es = 0;
+#pragma unroll
+    for (int e = 0; e < per; ++e)
+      if (lane * per + e < G * NW) {
+        const uint2 c = tab[lane * per + e];
+        gs += c.x;
+        es += c.y;
+      }
+    uint32_t gi = gs, ei = es;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t p = __shfl_up(gi, off), q = __shfl_up(ei, off);
+      if (lane >= off) {
+        gi += p;
+        ei += q;
       }
     }
-    uint32_t total;
-    const uint32_t ex = block_scan((gtc << 16) | eqc, scan_sh, total);
-    uint32_t gx = gt_run + (ex >> 16), qx = eq_run + (ex & 0xFFFFu);
+    gi -= gs;
+    ei -= es;
 #pragma unroll
-    for (int e = 0; e < kPerThread; ++e) {
-      const int64_t i = i0 + e;
-      if (i >= nb) break;
-      if (keys[e] > T) {
-        const uint32_t pos = gx + (qx < need ? qx : need);
-        if (pos < (uint32_t)k) out[pos] = (int32_t)i;
-        ++gx;
-      } else if (keys[e] == T) {
-        if (qx < need && gx + qx < (uint32_t)k) out[gx + qx] = (int32_t)i;
-        ++qx;
+    for (int e = 0; e < per; ++e)
+      if (lane * per + e < G * NW) {
+        const uint2 c = tab[lane * per + e];
+        tab[lane * per + e] = make_uint2(gi, ei);
+        gi += c.x;
+        ei += c.y;
+      }
+  }
+  __syncthreads();
+  int32_t* out = a.kept + (int64_t)seg * a.k_tot + a.kept_off[b];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int t = tok_of(g);
+    uint32_t gm = 0, em = 0, gb = 0, eb = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool gt = key[4 * g + j] > T, eq = key[4 * g + j] == T;
+      gm |= gt ? 1u << j : 0u;
+      em |= eq ? 1u << j : 0u;
+      gb += lanes_below(__builtin_amdgcn_ballot_w64(gt));
+      eb += lanes_below(__builtin_amdgcn_ballot_w64(eq));
+    }
+    if (gm | em) {
+      const uint2 st = tab[g * NW + wave];
+      uint32_t gx = st.x + gb, qx = st.y + eb;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if ((gm >> j) & 1u) {
+          const uint32_t pos = gx + (qx < need ? qx : need);
+          if (pos < k) out[pos] = t + j;
+          ++gx;
+        } else if ((em >> j) & 1u) {
+          if (qx < need && gx + qx < k) out[gx + qx] = t + j;
+          ++qx;
+        }
       }
     }
-    gt_run += total >> 16;
-    eq_run += total & 0xFFFFu;
   }
 }
 
 // ---------------------------------------------------------------------------- split selection
-// The same selection with each segment's tokens cut into parts of kSelPartTokens, so a
+// Longer segments: each segment's tokens are cut into parts of kSelPartTokens, so a
 // segment is worked on by several workgroups, each of which handles its part in one step (all
 // of its loads in flight together).  No workgroup waits for another (five launches, each
 // reading what the previous ones wrote), and only integer counts are combined, so the result
 // does not depend on the order in which workgroups run:
+//   k_sel_norms    (normalised-add rule only) per part: the sums of squares of its two signals;
 //   k_sel_score    per part: (pooling of pass 2's raw sums, when fused) the combined score S,
 //                  written once, and the part's histogram of the 12-bit top digit of its keys;
 //   k_sel_pick     per segment: the parts' histograms summed, the top digit of the k-th key;
@@ -317,11 +452,6 @@ static_assert(kSelPartTokens == kPartThreads * kScorePer && kSelPartTokens == kE
 // Count of bin `bin` in a part's packed histogram.
 __device__ inline uint32_t part_count(const uint32_t* hp, uint32_t bin) {
   return (hp[bin >> 1] >> (16 * (bin & 1))) & 0xFFFFu;
-}
-
-// Lanes below this one in a wave's ballot mask.
-__device__ inline uint32_t lanes_below(uint64_t m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 struct PartRange {
@@ -359,6 +489,46 @@ __device__ inline float window_sum(const float* tile, int l, int h) {
   return acc;
 }
 
+// The normalised-add rule's partial sums of squares of part p, in fp64 (key scores, scales).  They
+// take the places of the part's pcount and pref entries, which later kernels write.
+static_assert(sizeof(uint2) == sizeof(double), "a partial sum per entry");
+
+__global__ __launch_bounds__(kPartThreads) void k_sel_norms(SelectArgs a) {
+  const int p = blockIdx.x, seg = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  PartRange r;
+  if (!part_range(a, p, b, r)) return;
+  const int64_t base = (int64_t)seg * a.n_tot + r.n0;
+  double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+  for (int e = 0; e < kScorePer; ++e) {
+    const int64_t i = r.i0 + tid + kPartThreads * e;
+    const double x = i < r.i1 ? a.s_key[base + i] : 0.f, y = i < r.i1 ? a.scales[base + i] : 0.f;
+    s1 += x * x;
+    s2 += y * y;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    s1 += __shfl_xor(s1, off);
+    s2 += __shfl_xor(s2, off);
+  }
+  __shared__ double red[kPartThreads / 64][2];
+  if ((tid & 63) == 0) {
+    red[tid >> 6][0] = s1;
+    red[tid >> 6][1] = s2;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double t1 = 0.0, t2 = 0.0;
+    for (int w = 0; w < kPartThreads / 64; ++w) {
+      t1 += red[w][0];
+      t2 += red[w][1];
+    }
+    const int64_t slot = (int64_t)seg * a.part_tot + a.part_off[b] + p;
+    ((double*)a.pcount)[slot] = t1;
+    ((double*)a.pref)[slot] = t2;
+  }
+}
+
 // HALF: the pooling half-width this instance is specialised for (-1: any width up to
 // kPoolHaloMax staged in LDS, -2: wider windows summed from memory, -3: no pooling here, the
 // key score is read).
@@ -376,6 +546,17 @@ __global__ __launch_bounds__(kPartThreads) void k_sel_score(SelectArgs a, int se
   const int half = HALF >= 0 ? HALF : a.pool_half;
   const int nrg = a.nrg[b];
   const int64_t rstride = (int64_t)segments * a.n_tot;  // one row group's [L*Hkv][N_tot]
+  double norm_a = 0.0, norm_b = 0.0;
+  if (HALF == -3 && a.rule == TP_COMBINE_NORM_ADD) {  // the parts' partial sums, added in order
+    const int64_t slot = (int64_t)seg * a.part_tot + a.part_off[b];
+    const int np = parts_of(r.nb);
+    for (int q = 0; q < np; ++q) {
+      norm_a += ((const double*)a.pcount)[slot + q];
+      norm_b += ((const double*)a.pref)[slot + q];
+    }
+    norm_a = inverse_norm(norm_a);
+    norm_b = inverse_norm(norm_b);
+  }
   float sk[kScorePer], g[kScorePer];
   // every load of the part in flight together: the scales, and the raw sums of the part and
   // its halo into LDS (zero outside the sequence) or the key scores
@@ -431,7 +612,7 @@ __global__ __launch_bounds__(kPartThreads) void k_sel_score(SelectArgs a, int se
     const int l = tid + kPartThreads * e;
     if (l < ntok) {
       if (HALF != -3) a.s_key_out[base + r.i0 + l] = sk[e];
-      const float S = combine(a.rule, sk[e], g[e], 0.0, 0.0);
+      const float S = combine(a.rule, sk[e], g[e], norm_a, norm_b);
       a.s_buf[base + r.i0 + l] = S;
       atomicAdd(&hist[order_key(S) >> (32 - kTopBits)], 1u);
     }
@@ -845,8 +1026,54 @@ SelectWorkspace select_workspace_layout(int64_t segments, const int64_t* ctx_off
   return w;
 }
 
+// k_sel_one's rule: every segment's tokens, with the up to 3 slots that its misalignment costs,
+// fit one workgroup's registers, and a pooling window spans adjacent lanes only.  Up to 32768
+// tokens the one launch beats the split's five whatever the number of segments (us for the
+// whole selection, split against one: 8 segments of 8192 tokens 38.0 / 10.0, 8 of 32768 39.6 /
+// 24.1, 256 of 32768 64.7 / 34.9); up to 65536 only where the segments fill part of the chip
+// (8 segments 40.3 / 38.9, 64 49.5 / 49.4, 256 102 / 65.8, 300
+// 124 / 111).  Normalised-add against the former one-workgroup kernel, which read the scores
+// from memory four times: 32 of 32768 60.6 -> 29.7, 256 of 65536 120 -> 83.
+static int one_span(const SelectArgs& a, int segments) {
+  if (a.raw != nullptr && a.pool_half > kOneHalfMax) return 0;
+  int64_t most = 0;
+  bool aligned = (a.n_tot & 3) == 0 || segments == 1;
+  for (int b = 0; b < a.bt.batch; ++b) {
+    most = std::max(most, a.bt.ctx_off[b + 1] - a.bt.ctx_off[b]);
+    aligned = aligned && (a.bt.ctx_off[b] & 3) == 0;
+  }
+  if (!aligned) most += 3;
+  if (most > 32768 && (int64_t)segments * a.bt.batch < 96) return 0;
+  return most <= 65536 ? (int)most : 0;
+}
+
+template <int NT, int G>
+static void launch_one(const SelectArgs& a, int seg_begin, int seg_end, int segments, hipStream_t stream) {
+  const dim3 grid((unsigned)(seg_end - seg_begin), (unsigned)a.bt.batch), block(NT);
+  if (a.raw == nullptr)
+    hipLaunchKernelGGL((k_sel_one<NT, G, kReadScore>), grid, block, 0, stream, a, seg_begin, segments);
+  else if (a.pool_half == 2)  // pooling kernel 5, the benches' choice
+    hipLaunchKernelGGL((k_sel_one<NT, G, 2>), grid, block, 0, stream, a, seg_begin, segments);
+  else
+    hipLaunchKernelGGL((k_sel_one<NT, G, kAnyHalf>), grid, block, 0, stream, a, seg_begin, segments);
+}
+
 hipError_t launch_select_score(const SelectArgs& a, int seg_begin, int seg_end, int segments, hipStream_t stream) {
-  if (a.rule == TP_COMBINE_NORM_ADD || seg_end <= seg_begin) return hipSuccess;  // k_select forms S itself
+  if (seg_end <= seg_begin) return hipSuccess;
+  const int span = one_span(a, segments);
+  if (span > 0) {  // the whole selection of these segments
+    if (span <= 4096)
+      launch_one<256, 4>(a, seg_begin, seg_end, segments, stream);
+    else if (span <= 8192)
+      launch_one<1024, 2>(a, seg_begin, seg_end, segments, stream);
+    else if (span <= 16384)
+      launch_one<1024, 4>(a, seg_begin, seg_end, segments, stream);
+    else if (span <= 32768)
+      launch_one<1024, 8>(a, seg_begin, seg_end, segments, stream);
+    else
+      launch_one<1024, 16>(a, seg_begin, seg_end, segments, stream);
+    return hipGetLastError();
+  }
   const dim3 parts((unsigned)a.part_max, (unsigned)(seg_end - seg_begin), (unsigned)a.bt.batch);
   const dim3 pb(kPartThreads);
   if (a.raw == nullptr)
@@ -863,22 +1090,18 @@ hipError_t launch_select_score(const SelectArgs& a, int seg_begin, int seg_end, 
 }
 
 hipError_t launch_select(const SelectArgs& a, int segments, hipStream_t stream, hipEvent_t after_score,
-                         int scored_begin, int scored_end) {
+                         int scored) {
   const dim3 segs((unsigned)segments, (unsigned)a.bt.batch);
-  if (a.rule == TP_COMBINE_NORM_ADD) {  // the segment's norms come first: one workgroup per segment
-    if (after_score) {
-      const hipError_t e = hipEventRecord(after_score, stream);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_select, segs, dim3(kSelThreads), 0, stream, a);
-    return hipGetLastError();
-  }
   const dim3 parts((unsigned)a.part_max, (unsigned)segments, (unsigned)a.bt.batch);
-  if (scored_end <= scored_begin) scored_begin = scored_end = 0;
-  hipError_t e = launch_select_score(a, 0, scored_begin, segments, stream);
-  if (e == hipSuccess) e = launch_select_score(a, scored_end, segments, segments, stream);
+  const bool one = one_span(a, segments) > 0;
+  hipError_t e = hipSuccess;
+  if (!one && a.rule == TP_COMBINE_NORM_ADD) {
+    hipLaunchKernelGGL(k_sel_norms, parts, dim3(kPartThreads), 0, stream, a);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = launch_select_score(a, scored, segments, segments, stream);
   if (e == hipSuccess && after_score) e = hipEventRecord(after_score, stream);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || one) return e;
   hipLaunchKernelGGL(k_sel_pick, segs, dim3(kSelThreads), 0, stream, a);
   hipLaunchKernelGGL(k_sel_collect, parts, dim3(kPartThreads), 0, stream, a);
   hipLaunchKernelGGL(k_sel_refine, segs, dim3(kSelThreads), 0, stream, a);

@@ -29,17 +29,20 @@ constexpr int kRowsPerGroup = 256;       // guide rows handled by one workgroup
 constexpr int kChunkUnit = 256;
 int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off, int32_t batch);
 
-// Chunk of one sequence of n tokens under the call's `target`: the sequence is cut into
-// ceil(n / target) equal parts, rounded up to kChunkUnit (so never above the target), instead
-// of full chunks and a remainder whose workgroups end early.  n <= 2^30.
-__host__ __device__ inline int32_t balanced_chunk(int64_t n, int32_t target) {
+// Chunk of one sequence of n <= 2^30 tokens under the call's `target`.  Targets from 8192 up (calls of
+// many rounds of workgroups) cut full chunks and a remainder, whose short workgroups fill the
+// last round; shorter targets (few rounds) cut ceil(n / target) equal parts, rounded up to
+// kChunkUnit (so never above the target).
+constexpr int kChunkWhole = 8192;
+__host__ __device__ inline int32_t seq_chunk(int64_t n, int32_t target) {
+  if (target >= kChunkWhole) return target;
   const uint32_t parts = ((uint32_t)n + (uint32_t)target - 1u) / (uint32_t)target;
   const uint32_t per = ((uint32_t)n + parts - 1u) / parts;
   return (int32_t)((per + kChunkUnit - 1u) & ~(uint32_t)(kChunkUnit - 1));
 }
 // Chunks of a sequence of n tokens (never more than ceil(n / target)).
 __host__ __device__ inline int32_t chunks_of(int64_t n, int32_t target) {
-  const uint32_t c = (uint32_t)balanced_chunk(n, target);
+  const uint32_t c = (uint32_t)seq_chunk(n, target);
   return (int32_t)(((uint32_t)n + c - 1u) / c);
 }
 
@@ -125,8 +128,10 @@ hipError_t launch_quantize(const QuantArgs& a, int head_dim, hipStream_t stream)
 
 // The same quantisation in a form that stays resident beside a score-pass workgroup (one
 // workgroup per CU, one wave per SIMD, at most 48 VGPRs), for running part of step 2 on a
-// second stream concurrently with the score passes.
-hipError_t launch_quantize_lean(const QuantArgs& a, int head_dim, hipStream_t stream);
+// second stream concurrently with the score passes; `blocks` workgroups, kLeanBlocks to fill
+// every CU once.
+constexpr unsigned kLeanBlocks = 256;
+hipError_t launch_quantize_lean(const QuantArgs& a, int head_dim, unsigned blocks, hipStream_t stream);
 
 // ---------------------------------------------------------------- guide rows' prefill attention
 // Context tokens per workgroup of the guide rows' attention: 32768 when every sequence has at
@@ -172,8 +177,8 @@ AttnWorkspace attn_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, int32_t 
 hipError_t launch_guide_attention(const AttnArgs& a, int head_dim, hipStream_t stream);
 
 // ---------------------------------------------------------------- step 3 (select)
-// Every rule but NORM_ADD runs the split selection: each segment's tokens are cut into parts
-// of kSelPartTokens, one workgroup per part in the passes over the scores.
+// Segments too long for one workgroup run the split selection: each segment's tokens are cut
+// into parts of kSelPartTokens, one workgroup per part in the passes over the scores.
 constexpr int kSelPartTokens = 8192;
 constexpr int kSelCandCap = 8192;  // keys of the threshold's top-digit bucket kept per segment
 
@@ -219,12 +224,13 @@ struct SelectWorkspace {
 SelectWorkspace select_workspace_layout(int64_t segments, const int64_t* ctx_off, int32_t batch);
 
 // after_score (optional): recorded once the combined scores are formed (after the pooling
-// fused into the split selection, when `raw` is set).  [scored_begin, scored_end): segments
-// whose combined scores launch_select_score has already enqueued (the split selection only).
+// fused into the selection, when `raw` is set; where one workgroup selects a segment, after the
+// selection).  Segments before `scored` launch_select_score has already enqueued.
 hipError_t launch_select(const SelectArgs& a, int segments, hipStream_t stream, hipEvent_t after_score = nullptr,
-                         int scored_begin = 0, int scored_end = 0);
-// The split selection's first kernel for segments [seg_begin, seg_end) of `segments` (none for
-// NORM_ADD), so a caller can form the scores of segments whose inputs are ready early.
+                         int scored = 0);
+// The selection's first kernel for segments [seg_begin, seg_end) of `segments`, so a caller can
+// form the scores of segments whose inputs are ready early (not for NORM_ADD, whose norms
+// launch_select may have to form first).
 hipError_t launch_select_score(const SelectArgs& a, int seg_begin, int seg_end, int segments, hipStream_t stream);
 
 // The library's static staging buffer for the selection (tp_combine_select_topk_static): the

@@ -1,9 +1,15 @@
 """The launch rules that depend on sizes: each side of every line, on ragged and smallest shapes,
 against the CPU oracle (the comparison rules are parity_util's)."""
+import numpy as np
 import pytest
+import torch
 
 import synth
+from oracle import taskpress_oracle as o
+from paper_2608_03276_amd import binding as B
+from synth import workloads as W
 
+import parity_util as pu
 import test_gpu_parity as tgp
 
 pytestmark = pytest.mark.gpu
@@ -21,3 +27,96 @@ CHUNK_CASES = [
 @pytest.mark.parametrize("case", CHUNK_CASES, ids=[c[0] for c in CHUNK_CASES])
 def test_score_pass_chunks(gpu_lib, case, guide_keys):
     tgp._guide_case(case, guide_keys)
+
+
+def _select(rng, L, Hkv, lens, rule, ratio, budget, ties):
+    sk, g = tgp._select_inputs(rng, L, Hkv, lens, ties)
+    dd = B.dims(L, Hkv, Hkv, 64)
+    bt = B.Batch(np.concatenate([[0], np.cumsum(lens)]).tolist())
+    ko = B.kept_offsets_for(bt, ratio, budget)
+    kept = torch.full((L * Hkv * ko[-1],), -1, dtype=torch.int32, device="cuda")
+    s_out = torch.empty(L * Hkv * sum(lens), dtype=torch.float32, device="cuda")
+    B.tp_combine_select_topk(dd, bt, torch.from_numpy(sk).cuda(), torch.from_numpy(g).cuda(), rule, ratio, budget, ko,
+                             kept, s_out)
+    torch.cuda.synchronize()
+    S, kept = s_out.cpu().numpy().reshape(L * Hkv, -1), kept.cpu().numpy().reshape(L * Hkv, -1)
+    sk, g = sk.reshape(L * Hkv, -1), g.reshape(L * Hkv, -1)
+    for s in range(L * Hkv):
+        for b, n in enumerate(lens):
+            a, e = bt.ctx_offsets[b], bt.ctx_offsets[b + 1]
+            ref = o.combine(sk[s, a:e], g[s, a:e], rule)
+            tag = f"rule={rule} lens={lens} seg={s} b={b}"
+            if rule == o.COMBINE_NORM_ADD:  # fp64 norms summed in another order: at most an fp32 rounding apart
+                assert np.all(np.abs(S[s, a:e] - ref) <= 2.0 ** -23 * np.abs(ref)), tag
+            else:
+                assert np.array_equal(S[s, a:e].view(np.uint32), ref.view(np.uint32)), tag
+            # the kept set of the scores the call itself wrote, exactly
+            k = o.keep_count(n, ratio or None, budget or None)
+            assert np.array_equal(kept[s, ko[b]:ko[b + 1]], o.select(S[s, a:e], k)), tag
+
+
+# Each size class of the one-workgroup selection at its last aligned and first unaligned length
+# and one past it, and the split selection beyond 65536 tokens.
+SELECT_LENS = [[4096], [4093, 3], [4094, 3], [8192], [8190, 2, 7], [16384], [16381, 1], [32768], [32767, 5], [65536],
+               [65533, 1], [65534, 6], [65537], [100003, 70000, 1]]
+
+
+@pytest.mark.parametrize("rule", [0, 1, 2, 3])
+@pytest.mark.parametrize("lens", SELECT_LENS, ids=lambda v: "-".join(map(str, v)))
+def test_select_size_classes(gpu_lib, lens, rule):
+    rng = np.random.default_rng(71 + rule)
+    _select(rng, 1, 3, lens, rule, 0.13, 0, 0)
+    _select(rng, 1, 2, lens, rule, 0.0, 777, 5)  # five levels: ties at the threshold
+
+
+@pytest.mark.parametrize("lens", [[900], [4099, 3000], [20000, 33], [65530, 9], [66000, 12000]],
+                         ids=lambda v: "-".join(map(str, v)))
+@pytest.mark.parametrize("pool", [1, 3, 5, 7, 9, 11])
+def test_pooling_inside_selection(gpu_lib, lens, pool):
+    """tp_evict's selection pools the raw sums itself: bit for bit the pooling kernel's scores of
+    the separate calls (half-widths up to 4 across lanes, wider ones through LDS), one and two row groups."""
+    glens = [70] * len(lens)  # R * G = 280 rows: two row groups
+    w = W.Workload("pool", 1, 8, 2, 64, tuple(lens), tuple(glens), synth.Stream(81, synth.TAG_Q),
+                   synth.Stream(81, synth.TAG_K), synth.Stream(81, synth.TAG_V), keep_ratio=0.2, pool_k=pool)
+    q, k, v = pu.device_inputs(w)
+    a, b = pu.run_gpu(w, q, k, v, fused=True), pu.run_gpu(w, q, k, v, fused=False)
+    for name in ("s_key", "s_comb", "scales", "kept_idx", "k_c", "v_q_c", "scales_c"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+
+
+# tp_evict's second stream: V just below and just above each line (with pass 1; normalisers given),
+# bit for bit the separate calls, the overlapped ones also under capture and replayed.
+@pytest.mark.parametrize("given_lse,full_codes,heads", [(False, True, 79), (False, True, 80), (False, False, 80),
+                                                        (True, True, 127), (True, True, 128), (True, False, 129)])
+def test_evict_overlap_line(gpu_lib, given_lse, full_codes, heads):
+    w = W.Workload("line", 1, heads, heads, 128, (32768,), (8,), synth.Stream(91, synth.TAG_Q),
+                   synth.Stream(91, synth.TAG_K, synth.DIST_STUDENT_T3), synth.Stream(91, synth.TAG_V), keep_ratio=0.1)
+    assert heads * 32768 * 128 * 2 == heads * (8 << 20)  # V: 640 MB at 80 heads, 1 GB at 128
+    q, k, v = pu.device_inputs(w)
+    d, bt = B.dims(1, heads, heads, 128), B.Batch(w.ctx_offsets(), w.guide_offsets())
+    kw = dict(softmax_scale=w.softmax_scale, pool_k=5, qfmt=0, bits=8, keep_ratio=0.1)
+    names = ["s_key", "s_comb", "scales", "kept_idx", "k_c", "v_q_c", "scales_c"] + (["v_q"] if full_codes else [])
+    lse = None
+    ref = B.evict(d, bt, q, k, v, **kw)
+    if given_lse:  # the separate calls with these normalisers
+        lse = torch.linspace(9.0, 12.0, heads * 8, device="cuda")
+        B.tp_guide_scores_lse(d, bt, q, k, lse, w.softmax_scale, 5, ref.s_key, ref.ws_evict)
+        B.tp_combine_select_topk(d, bt, ref.s_key, ref.scales, 0, 0.1, 0, ref.kept_offsets, ref.kept_idx, ref.s_comb)
+        B.tp_compact_kv(d, bt, ref.kept_offsets, ref.kept_idx, k, ref.v_q, ref.scales, 0, 8, ref.k_c, ref.v_q_c,
+                        ref.scales_c)
+    got = B.EvictBuffers(d, bt, 0, 8, ref.kept_offsets)
+    B.evict_fused(d, bt, q, k, v, bufs=got, guide_lse=lse, full_codes=full_codes, **kw)
+    torch.cuda.synchronize()
+    for name in names:
+        assert torch.equal(getattr(got, name), getattr(ref, name)), name
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        B.evict_fused(d, bt, q, k, v, bufs=got, guide_lse=lse, full_codes=full_codes, **kw)
+    for _ in range(3):
+        for name in names:
+            getattr(got, name).zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for name in names:
+            assert torch.equal(getattr(got, name), getattr(ref, name)), name
