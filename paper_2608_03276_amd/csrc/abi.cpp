@@ -578,7 +578,7 @@ static tp_status guide_attention(const tp_dims* dims, const tp_batch* batch, con
   a.n_tot = batch->ctx_offsets[batch->batch];
   a.g_tot = batch->guide_offsets[batch->batch];
   a.c = (float)((double)softmax_scale * 1.4426950408889634);
-  a.chunk = tp::attn_chunk_tokens(batch->ctx_offsets, batch->batch);
+  a.chunk = lay.chunk;
   int64_t max_nb = 0, max_gb = 0;
   for (int b = 0; b < batch->batch; ++b) {
     max_nb = std::max<int64_t>(max_nb, batch->ctx_offsets[b + 1] - batch->ctx_offsets[b]);

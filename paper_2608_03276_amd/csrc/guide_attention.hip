@@ -8,7 +8,7 @@
 // Flash-attention style, split over the context in chunks: one workgroup per (sequence,
 // layer, KV head, chunk, group of <= 256 guide rows), eight waves (two per SIMD, so that one
 // wave's exponentials overlap the other's MFMAs), wave w owning rows 32w .. 32w + 31.  The
-// chunk's 32-token sub-tiles of K and V stream through a ring of LDS slots filled by direct
+// chunk's (plan_attn_chunk) 32-token sub-tiles of K and V stream through a ring of LDS slots filled by direct
 // global->LDS copies issued several sub-tiles ahead (one barrier per pair of sub-tiles), and every
 // wave reads the whole sub-tile.  Per sub-tile, on v_mfma_f32_32x32x16_bf16:
 //   S^T = K Q^T (tokens on M, rows on N): a lane holds one row and 16 of the 32 tokens (its
@@ -29,6 +29,9 @@
 #include "tile_common.h"
 #include "tp_internal.h"
 
+#include <math.h>
+
+#include <algorithm>
 #include <type_traits>
 
 namespace tp {
@@ -36,6 +39,10 @@ namespace {
 
 constexpr int kAttnThreads = 512;  // 8 waves, two per SIMD, 32 rows each
 constexpr int kAttnWaves = kAttnThreads / 64;
+constexpr double kAttnCus = 256.0;         // workgroups in flight: one per CU
+constexpr double kAttnWgTokens = 270.0;    // a workgroup's fixed work in tokens (30 ns each at 256 rows)
+constexpr double kAttnMergeTokens = 0.008; // writing and merging one row's partial of one chunk, likewise
+constexpr double kAttnSlotTokens = 12.0;   // the merge's latency per chunk, likewise
 constexpr float kAttnLazyLimit = 4294967296.0f;  // 2^32: a lane's 16 terms against a stale maximum
 constexpr int kAttnNoQuant = -1;  // the instance that leaves V's step 2 to its own kernel
 
@@ -223,6 +230,7 @@ struct AttnUnit {
   int b, seg, l, h, rg, chunk;
   bool guide;              // the guide's own keys (causal) rather than a context chunk
   int64_t n0, nb, g0;
+  int64_t c0;              // the unit's first context token in the sequence
   int gb, rows, row0, nrows, ntok, slot;
 };
 
@@ -241,11 +249,11 @@ __device__ inline bool attn_unit(const AttnArgs& a, AttnUnit& u) {
   u.row0 = u.rg * kRowsPerGroup;
   if (u.row0 >= u.rows) return false;
   u.nrows = u.rows - u.row0 < kRowsPerGroup ? u.rows - u.row0 : kRowsPerGroup;
-  const int nch = (int)((u.nb + a.chunk - 1) / a.chunk);
-  if (u.chunk < nch) {
+  const int csize = seq_chunk<kAttnUnit>(u.nb, a.chunk);
+  u.c0 = (int64_t)u.chunk * csize;
+  if (u.c0 < u.nb) {
     u.guide = false;
-    const int64_t c0 = (int64_t)u.chunk * a.chunk;
-    u.ntok = (int)(u.nb - c0 < a.chunk ? u.nb - c0 : a.chunk);
+    u.ntok = (int)(u.nb - u.c0 < csize ? u.nb - u.c0 : csize);
     u.slot = u.chunk;
     return true;
   }
@@ -298,8 +306,8 @@ __global__ __launch_bounds__(kAttnThreads, 1) void k_guide_fwd(AttnArgs a) {
     ksrc = a.kg + ((int64_t)u.seg * a.g_tot + u.g0) * D;
     vsrc = a.vg + ((int64_t)u.seg * a.g_tot + u.g0) * D;
   } else {
-    ksrc = a.k + ((int64_t)u.seg * a.n_tot + u.n0 + (int64_t)u.chunk * a.chunk) * D;
-    vsrc = a.v + ((int64_t)u.seg * a.n_tot + u.n0 + (int64_t)u.chunk * a.chunk) * D;
+    ksrc = a.k + ((int64_t)u.seg * a.n_tot + u.n0 + u.c0) * D;
+    vsrc = a.v + ((int64_t)u.seg * a.n_tot + u.n0 + u.c0) * D;
   }
   const char* kb = (const char*)ksrc;
   const char* vb = (const char*)vsrc;
@@ -426,7 +434,7 @@ __global__ __launch_bounds__(kAttnThreads, 1) void k_guide_fwd(AttnArgs a) {
   // duration to land.
   const bool qwg = QUANT && !u.guide && u.rg == 0;
   const QuantFmt qfmt{a.qfmt == TP_QFMT_INT, a.qfmt == TP_QFMT_INT && a.bits <= 4, a.qmax};
-  const int64_t qrow0 = (int64_t)u.seg * a.n_tot + u.n0 + (int64_t)u.chunk * a.chunk;
+  const int64_t qrow0 = (int64_t)u.seg * a.n_tot + u.n0 + u.c0;
   const int qtl = 8 * (wave & 3) + lane / QLPT;  // the lane's row of its sub-tile
   const int qj = lane % QLPT;                     // and its first piece, QNP qj
   const auto quant_pair = [&](int t, int cur, int c1) {
@@ -534,23 +542,40 @@ __global__ __launch_bounds__(256) void k_guide_fwd_merge(AttnArgs a) {
   const int64_t qh = rem / gb, jj = rem - qh * gb;
   const int64_t grow = (l * a.Hq + qh) * a.g_tot + g0 + jj;
   const int64_t rows_tot = (int64_t)a.L * a.Hq * a.g_tot;
-  const int nch = (int)((nb + a.chunk - 1) / a.chunk);
+  const int nch = chunks_of<kAttnUnit>(nb, a.chunk);
   const int nslot = a.kg != nullptr ? nch + 1 : nch;
-  auto slot_of = [&](int c) { return c < nch ? c : a.nchunk_max; };
+  auto prow_of = [&](int c) { return (int64_t)(c < nch ? c : a.nchunk_max) * rows_tot + grow; };
+  // the lanes take the partial maxima in parallel; then the slots in order, kMergeLoads slots'
+  // loads in flight together (a row's time was the slots' latencies one after the other)
   float mstar = kNoMax;
-  for (int c = 0; c < nslot; ++c) mstar = fmaxf(mstar, a.pstat[(int64_t)slot_of(c) * rows_tot + grow].x);
-  float tot = 0.f;
-  float acc[D / 64] = {};
-  for (int c = 0; c < nslot; ++c) {
-    const int64_t prow = (int64_t)slot_of(c) * rows_tot + grow;
-    const float2 st = a.pstat[prow];
-    const float w = __builtin_amdgcn_exp2f(st.x - mstar);
-    tot += w * st.y;
+  for (int c = lane; c < nslot; c += 64) mstar = fmaxf(mstar, a.pstat[prow_of(c)].x);
 #pragma unroll
-    for (int e = 0; e < D / 64; ++e) acc[e] += w * a.po[prow * D + lane + 64 * e];
+  for (int off = 32; off > 0; off >>= 1) mstar = fmaxf(mstar, __shfl_xor(mstar, off));
+  constexpr int E = D / 64;  // output values per lane
+  constexpr int kMergeLoads = 8;
+  float tot = 0.f;
+  float acc[E] = {};
+  for (int c0 = 0; c0 < nslot; c0 += kMergeLoads) {
+    float2 st[kMergeLoads];
+    float v[kMergeLoads][E];
+#pragma unroll
+    for (int u = 0; u < kMergeLoads; ++u) {
+      const int64_t prow = prow_of(min(c0 + u, nslot - 1));
+      st[u] = a.pstat[prow];
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[u][e] = a.po[prow * D + E * lane + e];
+    }
+#pragma unroll
+    for (int u = 0; u < kMergeLoads; ++u) {
+      if (c0 + u >= nslot) break;
+      const float w = __builtin_amdgcn_exp2f(st[u].x - mstar);
+      tot += w * st[u].y;
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[e] += w * v[u][e];
+    }
   }
 #pragma unroll
-  for (int e = 0; e < D / 64; ++e) a.o[grow * D + lane + 64 * e] = acc[e] / tot;
+  for (int e = 0; e < E; ++e) a.o[grow * D + E * lane + e] = acc[e] / tot;
   if (lane == 0) a.lse[grow] = (mstar + log2f(tot)) * 0.69314718055994531f;
 }
 
@@ -577,17 +602,77 @@ void launch_fwd(const AttnArgs& a, dim3 grid, hipStream_t stream) {
 
 }  // namespace
 
+// The call's target chunk: 32768 when every sequence has at least 131072 tokens, else 8192; calls
+// that give it fewer than three rounds of workgroups (the guide units among them) take the chunk
+// with the least estimated time: for 1 to 4 rounds the shortest whose workgroups fit, and its
+// doublings, since every chunk's partial output is written and merged.  The attention with the
+// guide keys, us at 8192 and at the chunk chosen: one layer of 32q/8kv heads, 64 guide tokens, at
+// 17001 tokens 178 -> 47 (576), at 32768 175 -> 58 (1088), at 131072 203 -> 175 (4288); four
+// layers at 32768 195 -> 170 (4736); seven segments of 3924 tokens 92 -> 29 (256).
+int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off,
+                        int32_t batch) {
+  const int64_t R = Hq / Hkv, segs = (int64_t)L * Hkv;
+  bool all_long = true;
+  int64_t longest = 0;
+  for (int b = 0; b < batch; ++b) {
+    longest = std::max(longest, ctx_off[b + 1] - ctx_off[b]);
+    all_long = all_long && ctx_off[b + 1] - ctx_off[b] >= 131072;
+  }
+  const int32_t usual = all_long ? 32768 : 8192;
+  const double row_slots = (double)L * Hq * (double)g_off[batch];
+  struct Cost {
+    double time, rounds;
+  };
+  auto cost_of = [&](int32_t target) {
+    double wgs = 0.0;
+    int64_t most = 0;
+    for (int b = 0; b < batch; ++b) {
+      const int64_t n = ctx_off[b + 1] - ctx_off[b], rows = R * (g_off[b + 1] - g_off[b]);
+      wgs += (double)(segs * (chunks_of<kAttnUnit>(n, target) + 1)) * (double)((rows + kRowsPerGroup - 1) / kRowsPerGroup);
+      most = std::max<int64_t>(most, std::min<int64_t>(n, seq_chunk<kAttnUnit>(n, target)));
+    }
+    const double rounds = ceil(wgs / kAttnCus);
+    const double slots = (double)((longest + target - 1) / target);
+    return Cost{rounds * (kAttnWgTokens + (double)most) + slots * (row_slots * kAttnMergeTokens + kAttnSlotTokens),
+                rounds};
+  };
+  const Cost at_usual = cost_of(usual);
+  if (at_usual.rounds >= 3.0) return usual;
+  // for 1, 2, .. rounds of the chip, the shortest chunk whose workgroups fit them
+  int32_t best = usual;
+  double least = at_usual.time * 0.97;
+  for (int r = 1; r <= 4; ++r) {
+    int32_t lo = 1, hi = kChunkWhole / kAttnUnit - 1;  // in units; wgs falls as the chunk grows
+    while (lo < hi) {
+      const int32_t mid = (lo + hi) / 2;
+      if (cost_of(mid * kAttnUnit).rounds <= r)
+        hi = mid;
+      else
+        lo = mid + 1;
+    }
+    // and longer ones, where merging that many partial outputs would cost more
+    for (int32_t target = lo * kAttnUnit; target < kChunkWhole; target *= 2) {
+      const Cost c = cost_of(target);
+      if (c.time < least) {
+        best = target;
+        least = c.time;
+      }
+    }
+  }
+  return best;
+}
+
 AttnWorkspace attn_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_dim, const int64_t* ctx_off,
                                     const int64_t* g_off, int32_t batch) {
-  (void)Hkv;
   int64_t max_nb = 0;
   for (int b = 0; b < batch; ++b)
     if (ctx_off[b + 1] - ctx_off[b] > max_nb) max_nb = ctx_off[b + 1] - ctx_off[b];
-  const int64_t chunk = attn_chunk_tokens(ctx_off, batch);
+  const int32_t chunk = plan_attn_chunk(L, Hq, Hkv, ctx_off, g_off, batch);
   const int64_t nslot = (max_nb + chunk - 1) / chunk + 1;  // the context chunks, then the guide keys
   const int64_t rows = (int64_t)L * Hq * g_off[batch];
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   AttnWorkspace w;
+  w.chunk = chunk;
   w.pstat_off = 0;
   w.po_off = up((size_t)nslot * rows * sizeof(float2));
   w.total = w.po_off + up((size_t)nslot * rows * head_dim * sizeof(float));

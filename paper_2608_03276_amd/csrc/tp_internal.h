@@ -34,15 +34,17 @@ int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, c
 // last round; shorter targets (few rounds) cut ceil(n / target) equal parts, rounded up to
 // kChunkUnit (so never above the target).
 constexpr int kChunkWhole = 8192;
+template <int UNIT = kChunkUnit>
 __host__ __device__ inline int32_t seq_chunk(int64_t n, int32_t target) {
   if (target >= kChunkWhole) return target;
   const uint32_t parts = ((uint32_t)n + (uint32_t)target - 1u) / (uint32_t)target;
   const uint32_t per = ((uint32_t)n + parts - 1u) / parts;
-  return (int32_t)((per + kChunkUnit - 1u) & ~(uint32_t)(kChunkUnit - 1));
+  return (int32_t)((per + UNIT - 1u) & ~(uint32_t)(UNIT - 1));
 }
 // Chunks of a sequence of n tokens (never more than ceil(n / target)).
+template <int UNIT = kChunkUnit>
 __host__ __device__ inline int32_t chunks_of(int64_t n, int32_t target) {
-  const uint32_t c = (uint32_t)seq_chunk(n, target);
+  const uint32_t c = (uint32_t)seq_chunk<UNIT>(n, target);
   return (int32_t)(((uint32_t)n + c - 1u) / c);
 }
 
@@ -134,15 +136,12 @@ constexpr unsigned kLeanBlocks = 256;
 hipError_t launch_quantize_lean(const QuantArgs& a, int head_dim, unsigned blocks, hipStream_t stream);
 
 // ---------------------------------------------------------------- guide rows' prefill attention
-// Context tokens per workgroup of the guide rows' attention: 32768 when every sequence has at
-// least 131072 (fewer partial outputs to merge), else 8192.
-constexpr int kAttnChunkSmall = 8192;
-constexpr int kAttnChunkLarge = 32768;
-inline int32_t attn_chunk_tokens(const int64_t* ctx_off, int32_t batch) {
-  for (int b = 0; b < batch; ++b)
-    if (ctx_off[b + 1] - ctx_off[b] < 131072) return kAttnChunkSmall;
-  return kAttnChunkLarge;
-}
+// Context tokens per workgroup of the guide rows' attention, for a call: 32768 when every
+// sequence has at least 131072 (fewer partial outputs to merge), else 8192, shorter where that
+// leaves the chip idle; a multiple of kAttnUnit (a pair of 32-token sub-tiles) below 8192.
+constexpr int kAttnUnit = 64;
+int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off,
+                        int32_t batch);
 
 struct AttnArgs {
   const uint16_t* q;   // bf16 [L][Hq][G_tot][d]
@@ -157,8 +156,8 @@ struct AttnArgs {
   int32_t L, Hq, Hkv, R;
   int64_t n_tot, g_tot;
   float c;             // softmax_scale * log2(e)
-  int32_t chunk;       // attn_chunk_tokens of the batch
-  int32_t nchunk_max;  // chunks of the longest sequence
+  int32_t chunk;       // target context tokens per chunk (plan_attn_chunk of the call)
+  int32_t nchunk_max;  // slots of the context chunks: ceil(longest sequence / chunk)
   int32_t nrg_max;     // row groups of the largest R * G_b
   BatchArgs bt;
   // Step 2 from the staged V sub-tiles (tp_guide_attention_quantize); vq == nullptr: none.
@@ -171,6 +170,7 @@ struct AttnArgs {
 
 struct AttnWorkspace {
   size_t pstat_off, po_off, total;
+  int32_t chunk;  // plan_attn_chunk of the call, which the layout follows
 };
 AttnWorkspace attn_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_dim, const int64_t* ctx_off,
                                     const int64_t* g_off, int32_t batch);

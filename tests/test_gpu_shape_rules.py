@@ -10,6 +10,7 @@ from paper_2608_03276_amd import binding as B
 from synth import workloads as W
 
 import parity_util as pu
+import test_gpu_guide_attention as tga
 import test_gpu_parity as tgp
 
 pytestmark = pytest.mark.gpu
@@ -120,3 +121,34 @@ def test_evict_overlap_line(gpu_lib, given_lse, full_codes, heads):
         torch.cuda.synchronize()
         for name in names:
             assert torch.equal(getattr(got, name), getattr(ref, name)), name
+
+
+# Attention chunks: multiples of 64 tokens in calls of few workgroups, 8192 from three rounds on.
+ATTN_CASES = [
+    ("unit-edges", 1, 8, 2, 128, [63, 64, 65, 129, 700, 1], [16, 3, 64, 9, 33, 1], True),
+    ("even-cuts", 1, 8, 2, 64, [4097, 2333, 7681], [16, 80, 40], True),
+    ("many-slots", 1, 2, 1, 128, [12000], [5], False),  # more chunks than the merge loads at once
+    ("usual-chunk", 12, 64, 64, 64, [90, 8193], [2, 1], True),  # > 768 workgroups
+]
+
+
+@pytest.mark.parametrize("case", ATTN_CASES, ids=[c[0] for c in ATTN_CASES])
+def test_attention_chunks(gpu_lib, case):
+    w, guide_keys = tga._workload(case), case[-1]
+    (q, k, v, kg, vg), o_gpu, lse_gpu = tga._run_attention(w, guide_keys)
+    for l in {0, w.L - 1}:
+        for h in {0, w.Hkv - 1}:
+            for b in range(w.batch):
+                tga._check_rows(w, b, l, h, range(h * w.R, (h + 1) * w.R), o_gpu, lse_gpu, guide_keys)
+    # the quantising instance: the same attention and every token's scale and codes
+    d, bt = B.dims(w.L, w.Hq, w.Hkv, w.d), B.Batch(w.ctx_offsets(), w.guide_offsets())
+    n = w.L * w.Hkv * w.n_tot
+    out = torch.empty(o_gpu.size, device="cuda"), torch.empty(lse_gpu.size, device="cuda")
+    got = torch.full((n,), -1.0, device="cuda"), torch.full((n * w.d,), 77, dtype=torch.uint8, device="cuda")
+    ref = torch.empty(n, device="cuda"), torch.empty(n * w.d, dtype=torch.uint8, device="cuda")
+    B.tp_guide_attention_quantize(d, bt, q, k, v, w.softmax_scale, 0, 8, *out, *got, k_guide=kg, v_guide=vg)
+    B.tp_quantize_v_scales(d, bt, v, 0, 8, *ref)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0].cpu(), torch.from_numpy(o_gpu.ravel()))
+    assert torch.equal(out[1].cpu(), torch.from_numpy(lse_gpu.ravel()))
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
