@@ -19,10 +19,20 @@
 // A workgroup (8 waves, one per CU) takes one chunk of 256 to 16384 tokens (plan_chunk) and one
 // group of <= 256 guide rows.  The group's queries sit in LDS for the whole chunk.  Each wave streams its
 // own 32-token K sub-tiles: an asynchronous global->LDS copy into the wave's private
-// staging buffer runs while the wave computes the previous sub-tile from registers, so no
-// barrier is needed inside the main loop and the K fragments take no prefetch registers.
-// Inside a sub-tile the wave is software-pipelined: the MFMAs of one pair of 32-row blocks
-// run while the vector ALU does the softmax work of the previous pair.
+// staging buffer runs while the wave computes from registers, so no barrier is needed inside
+// the main loop and the K fragments take no prefetch registers.
+//
+// A wave holds two K tiles (a and b) and walks the group's row blocks in a circle, each query
+// fragment it reads from LDS serving both tiles.  The tiles are half a revolution apart: the
+// sub-tile that replaces a enters at row block 0, the one that replaces b at row block NP of
+// 2 NP, and each leaves after a whole revolution.  So one staging buffer per wave serves both
+// (two buffers would not fit beside the queries), a copy has half a revolution, 2 NP tile
+// products, to land, and the query reads from LDS are half of what one tile at a time takes.
+// They bound the passes next to the vector ALU and the power-limited clock.  tp_evict at 262144
+// tokens, 48 layers of 16q/2kv heads, 256 guide tokens: 27.3 ms with one tile at a time, 26.6 with
+// two, 25.5 with the copies' addresses out of the vector ALU as well (dma_whole).
+// Inside a half the wave is software-pipelined: the MFMAs of one row block run while the vector
+// ALU does the softmax work of the previous one.
 #include <math.h>
 
 #include <algorithm>
@@ -112,14 +122,15 @@ __device__ inline void stage_q(const GuideArgs& a, const Work& w, char* qs) {
   }
 }
 
-// Q fragment of local row block rb: row 32 rb + lane%32, the d-columns of this half-wave.
-template <int D>
+// k-steps [S0, S1) of the Q fragment of local row block rb: row 32 rb + lane%32, the d-columns of
+// this half-wave.
+template <int D, int S0, int S1>
 __device__ inline void read_qfrag(const char* qs, int rb, Frag (&qf)[Cfg<D>::kSteps]) {
   using C = Cfg<D>;
   const int lane = threadIdx.x & 63;
   const char* base = qs + (lane & 31) * C::kStride + (lane >> 5) * C::kRowBytes / 2 + rb * 32 * C::kStride;
 #pragma unroll
-  for (int s = 0; s < C::kSteps; ++s) qf[s].u = *(const uint4*)(base + 16 * s);
+  for (int s = S0; s < S1; ++s) qf[s].u = *(const uint4*)(base + 16 * s);
 }
 
 // Issue the copy of the sub-tile starting at chunk token t0 into `kbuf`: each instruction
@@ -138,6 +149,27 @@ __device__ inline void dma_subtile(const char* kchunk, int t0, int ntok, char* k
     const char* src = kchunk + (uint32_t)tok * C::kRowBytes + p * 16;
     __builtin_amdgcn_global_load_lds((const void*)src, (__attribute__((address_space(3))) void*)(kbuf + j * 1024), 16,
                                      0, 0);
+  }
+}
+
+// The same for a sub-tile whose 32 tokens all exist: copy j reads from a wave-uniform base and the
+// lane's fixed offset, whose swizzle differs between copies only in piece bit 2, 3 or both
+// (j * kTokPerKB enters swz there), so a whole sub-tile takes a few vector instructions instead
+// of about ninety.  Inline assembly for the scalar-base form; completion is tracked by
+// wait_copies.  One wait state separates the M0 write from the copy that reads it.
+template <int D>
+__device__ inline void dma_whole(const char* kchunk, int t0, uint32_t kbuf_lds) {
+  using C = Cfg<D>;
+  const int lane = threadIdx.x & 63;
+  const int tl0 = lane / C::kPieces;
+  const uint32_t off0 = (uint32_t)(tl0 * C::kRowBytes + ((lane % C::kPieces) ^ swz<D>(tl0)) * 16);
+  const char* base = kchunk + (int64_t)t0 * C::kRowBytes;
+#pragma unroll
+  for (int j = 0; j < 32 / C::kTokPerKB; ++j) {
+    const uint32_t flip = (uint32_t)swz<D>(j * C::kTokPerKB) * 16;
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off0 ^ flip),
+                 "s"(base + j * 1024), "s"(kbuf_lds + (uint32_t)j * 1024u)
+                 : "memory", "m0");
   }
 }
 
@@ -160,47 +192,61 @@ __device__ inline void balance_issue(int* progress, int wave, int done) {
 // The staging buffer has landed (the wave's copies are complete).  The memory clobber keeps
 // the compiler from moving LDS reads of the buffer above the wait.
 __device__ inline void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// The fragment reads of the buffer are complete, so it may be overwritten.
-__device__ inline void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// The fragment reads of the buffer are complete, so it may be overwritten.  The builtin tells the
+// compiler so, which then adds no wait of its own at the fragments' first uses (there it would
+// also wait for the query reads issued since).
+__device__ inline void wait_lds_reads() {
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
 
-// Two independent MFMA chains: row blocks rb, rb+1 against one K sub-tile.  With INIT the
-// chains accumulate onto the values already in c0, c1; otherwise they start from zero.
-template <int KS, bool Q_IS_A, bool INIT = false>
-__device__ inline void mfma_pair(const Frag (&q0)[KS], const Frag (&q1)[KS], const Frag (&k)[KS], f32x16& c0,
-                                 f32x16& c1) {
-  if (!INIT) {
-    c0 = (f32x16){};
-    c1 = (f32x16){};
-  }
+// Which of the wave's two K tiles a step computes: both, or one (the wave's first and last half
+// revolutions).
+constexpr int kBothTiles = 0, kOnlyA = 1, kOnlyB = 2;
+
+// One row block against the wave's K tiles a and b: two independent MFMA chains that share the
+// query fragment.  The chains start from `init`; a tile left out gives -inf (an empty slot).
+template <int KS, bool Q_IS_A, int TILES>
+__device__ inline void mfma_tiles(const Frag (&q)[KS], const Frag (&ka)[KS], const Frag (&kb)[KS], const f32x16& init,
+                                  f32x16& c0, f32x16& c1) {
+  c0 = init;
+  c1 = init;
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
-    if (Q_IS_A) {
-      c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[s].v, k[s].v, c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q1[s].v, k[s].v, c1, 0, 0, 0);
-    } else {
-      c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k[s].v, q0[s].v, c0, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k[s].v, q1[s].v, c1, 0, 0, 0);
-    }
+    if (TILES != kOnlyB)
+      c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Q_IS_A ? q[s].v : ka[s].v, Q_IS_A ? ka[s].v : q[s].v, c0, 0, 0, 0);
+    if (TILES != kOnlyA)
+      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Q_IS_A ? q[s].v : kb[s].v, Q_IS_A ? kb[s].v : q[s].v, c1, 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if (TILES == kOnlyB) c0[i] = -INFINITY;
+    if (TILES == kOnlyA) c1[i] = -INFINITY;
   }
 }
 
-// Instruction order of one pipeline step: NDS0 LDS reads first, then a little vector work
-// (NV0 plain, NT0 transcendental instructions) while they land, then each MFMA followed by
-// an even share of the remaining vector work of the previous pair (NV plain, NT
-// transcendental, counted separately because the scheduler classes them separately) and
-// one of the NDS LDS reads that fetch the next step's query fragments.  The matrix core,
-// the vector ALU and the LDS stay busy together, and the LDS latency is covered by a step.
-template <int NDS0, int NV0, int NT0, int NDS, int NMFMA, int NV, int NT>
+// The last kLateQ k-steps of a row block's query fragment are read after the first MFMAs of its own
+// step, the others during the step before, each once its predecessor has been consumed: the
+// first MFMA of a step waits for every LDS read issued before it, so none may be issued late.
+constexpr int kLateQ = 2;
+
+// Instruction order of one pipeline step: each MFMA followed by an even share of the vector work of
+// the previous step (NV plain, NT transcendental, counted separately because the scheduler
+// classes them separately) and by LDS reads: the late query reads, the next step's query
+// fragment as this one's is consumed and, with Z, its four start values (pass 2).  The matrix
+// core, the vector ALU and the LDS stay busy together, and the LDS latency is covered.
+template <int KS, int NMFMA, int NV, int NT, bool Z>
 __device__ inline void step_schedule() {
-  if (NDS0 > 0) __builtin_amdgcn_sched_group_barrier(0x100, NDS0, 0);
-  if (NV0 > 0) __builtin_amdgcn_sched_group_barrier(0x002, NV0, 0);
-  if (NT0 > 0) __builtin_amdgcn_sched_group_barrier(0x400, NT0, 0);
+  constexpr int kPer = NMFMA / KS;  // MFMAs per query fragment
 #pragma unroll
   for (int i = 0; i < NMFMA; ++i) {
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     __builtin_amdgcn_sched_group_barrier(0x002, NV, 0);
     __builtin_amdgcn_sched_group_barrier(0x400, NT, 0);
-    if (i < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    if (i < kLateQ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    const bool refill = (i + 1) % kPer == 0 && (i + 1) / kPer < KS - kLateQ;
+    if (refill || i == kPer * (KS - kLateQ)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    if (Z && i % kPer == 0 && i >= kPer && i <= 4 * kPer) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
 }
@@ -246,34 +292,34 @@ __device__ inline float unit_sum(const f32x16& acc, float c, float m) {
 // rescaling from the common case.
 constexpr float kLazyLimit = 18446744073709551616.0f;  // 2^64
 
-// One sub-tile of pass 1, software-pipelined over the NP row-block pairs: step p issues the
-// MFMAs of pair p (query fragments qa, qb, fetched during the previous step) while the
-// vector ALU turns the pending pair (pair p-1, or the previous sub-tile's last pair when
-// p = 0) into row statistics and the LDS delivers the query fragments of the next pair.
-template <int D, int NP>
-__device__ inline void stats_steps(const char* qs, const Frag (&kf)[Cfg<D>::kSteps], Frag (&qa)[Cfg<D>::kSteps],
-                                   Frag (&qb)[Cfg<D>::kSteps], f32x16& p0, f32x16& p1, float (&sm)[2 * NP],
-                                   float (&ss)[2 * NP], float c) {
-  using C = Cfg<D>;
-  constexpr int NM = 2 * C::kSteps;  // MFMAs per step
+// Half a revolution of pass 1 (see the head of the file): row blocks H NP .. H NP + NP - 1
+// against the wave's two K tiles.  Step p issues the MFMAs of its row block (query fragment q,
+// fetched during the previous step) while the vector ALU turns the pending results (the row block
+// before, both tiles) into row statistics and the LDS delivers the next block's query fragment.
+template <int D, int NP, int H, int TILES>
+__device__ inline void stats_half(const char* qs, const Frag (&ka)[Cfg<D>::kSteps], const Frag (&kb)[Cfg<D>::kSteps],
+                                  Frag (&q)[Cfg<D>::kSteps], f32x16& p0, f32x16& p1, float (&sm)[2 * NP],
+                                  float (&ss)[2 * NP], float c) {
+  constexpr int KS = Cfg<D>::kSteps;
+  constexpr int NM = TILES == kBothTiles ? 2 * KS : KS;  // MFMAs per step
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     f32x16 n0, n1;
-    mfma_pair<C::kSteps, false>(qa, qb, kf, n0, n1);
-    const int pn = p + 1 < NP ? p + 1 : 0;
-    read_qfrag<D>(qs, 2 * pn, qa);
-    read_qfrag<D>(qs, 2 * pn + 1, qb);
-    const int rb = p == 0 ? 2 * NP - 2 : 2 * p - 2;
-    const float t0 = unit_sum(p0, c, sm[rb]), t1 = unit_sum(p1, c, sm[rb + 1]);
-    const bool big0 = !(t0 < kLazyLimit), big1 = !(t1 < kLazyLimit);
-    ss[rb] += big0 ? 0.f : t0;
-    ss[rb + 1] += big1 ? 0.f : t1;
-    pin(ss[rb], ss[rb + 1], t0, t1);
-    // 2 x (16 fma + 15 add) + compares, selects and adds; 32 exp2
-    step_schedule<0, 0, 0, NM, NM, (68 + NM - 1) / NM, 32 / NM>();
-    if (__builtin_amdgcn_ballot_w64(big0 || big1)) {  // rare: exact update of those units
-      if (big0) stats_update(p0, c, sm[rb], ss[rb]);
-      if (big1) stats_update(p1, c, sm[rb + 1], ss[rb + 1]);
+    read_qfrag<D, KS - kLateQ, KS>(qs, H * NP + p, q);
+    mfma_tiles<KS, false, TILES>(q, ka, kb, (f32x16){}, n0, n1);
+    read_qfrag<D, 0, KS - kLateQ>(qs, (H * NP + p + 1) % (2 * NP), q);
+    const int rb = (H * NP + p + 2 * NP - 1) % (2 * NP);
+    const float t = unit_sum(p0, c, sm[rb]) + unit_sum(p1, c, sm[rb]);
+    const bool big = !(t < kLazyLimit);
+    ss[rb] += big ? 0.f : t;
+    pin(ss[rb], t, t, t);
+    // 2 x (16 fma + 15 add) + compare, select and adds; 32 exp2
+    step_schedule<KS, NM, (66 + NM - 1) / NM, 32 / NM, false>();
+    if (__builtin_amdgcn_ballot_w64(big)) {  // rare: exact update of those units
+      if (big) {
+        stats_update(p0, c, sm[rb], ss[rb]);
+        stats_update(p1, c, sm[rb], ss[rb]);
+      }
     }
     p0 = n0;
     p1 = n1;
@@ -287,20 +333,17 @@ __device__ inline void stats_tail(const char* qs, const Frag (&kf)[Cfg<D>::kStep
   using C = Cfg<D>;
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    Frag q0[C::kSteps], q1[C::kSteps];
-    read_qfrag<D>(qs, 2 * p, q0);
-    read_qfrag<D>(qs, 2 * p + 1, q1);
-    f32x16 a0, a1;
-    mfma_pair<C::kSteps, false>(q0, q1, kf, a0, a1);
+  for (int rb = 0; rb < 2 * NP; ++rb) {
+    Frag q[C::kSteps];
+    read_qfrag<D, 0, C::kSteps>(qs, rb, q);
+    f32x16 x, none;
+    mfma_tiles<C::kSteps, false, kOnlyA>(q, kf, kf, (f32x16){}, x, none);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int tok = (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3);
-      a0[i] = tok < nvalid ? a0[i] : -INFINITY;
-      a1[i] = tok < nvalid ? a1[i] : -INFINITY;
+      x[i] = tok < nvalid ? x[i] : -INFINITY;
     }
-    stats_update(a0, c, sm[2 * p], ss[2 * p]);
-    stats_update(a1, c, sm[2 * p + 1], ss[2 * p + 1]);
+    stats_update(x, c, sm[rb], ss[rb]);
   }
 }
 
@@ -315,6 +358,7 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_stats(GuideArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
   char* kbuf = kst + wave * C::kStageBytes;
+  const uint32_t kbuf_lds = (uint32_t)uniform((int)(uintptr_t)(__attribute__((address_space(3))) char*)kbuf);
   const char* kchunk = (const char*)(a.k + ((int64_t)w.seg * a.n_tot + w.n0 + w.c0) * D);
   const int ntok = (int)(w.c1 - w.c0);
   const int nfull = ntok / 32;
@@ -329,32 +373,54 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_stats(GuideArgs a) {
     sm[i] = kNoMax;
     ss[i] = 0.f;
   }
-  // full sub-tiles st = wave, wave + 8, ...
-  Frag kf[C::kSteps], qa[C::kSteps], qb[C::kSteps];
+  // full sub-tiles st = wave, wave + 8, ..., into tiles a and b in turn
+  Frag ka[C::kSteps], kb[C::kSteps], q[C::kSteps];
   f32x16 p0, p1;
 #pragma unroll
   for (int i = 0; i < 16; ++i) p0[i] = p1[i] = -INFINITY;  // empty pipeline slot
-  read_qfrag<D>(qs, 0, qa);
-  read_qfrag<D>(qs, 1, qb);
+  read_qfrag<D, 0, C::kSteps - kLateQ>(qs, 0, q);
   __shared__ int progress[kGuideWaves];
   if (threadIdx.x < kGuideWaves) progress[threadIdx.x] = 0;
   __syncthreads();
-  for (int done = 0; st < nfull; st += kGuideWaves) {
+  int done = 0;
+  const auto next_tile = [&](Frag(&kf)[C::kSteps]) {
     wait_copies();
     read_kfrag<D>(kbuf, kf);
     wait_lds_reads();
-    if (st + kGuideWaves < nfull) dma_subtile<D>(kchunk, 32 * (st + kGuideWaves), ntok, kbuf);
-    stats_steps<D, NP>(qs, kf, qa, qb, p0, p1, sm, ss, a.c);
+    st += kGuideWaves;
+    if (st < nfull) dma_whole<D>(kchunk, 32 * st, kbuf_lds);
+    __builtin_amdgcn_sched_barrier(0);  // the step's LDS slots are for the query fragments
+  };
+  if (st < nfull) {
+    next_tile(ka);
+    stats_half<D, NP, 0, kOnlyA>(qs, ka, kb, q, p0, p1, sm, ss, a.c);
     balance_issue(progress, wave, ++done);
+    while (st + kGuideWaves < nfull) {  // two more tiles
+      next_tile(kb);
+      stats_half<D, NP, 1, kBothTiles>(qs, ka, kb, q, p0, p1, sm, ss, a.c);
+      balance_issue(progress, wave, ++done);
+      next_tile(ka);
+      stats_half<D, NP, 0, kBothTiles>(qs, ka, kb, q, p0, p1, sm, ss, a.c);
+      balance_issue(progress, wave, ++done);
+    }
+    if (st < nfull) {
+      next_tile(kb);
+      stats_half<D, NP, 1, kBothTiles>(qs, ka, kb, q, p0, p1, sm, ss, a.c);
+      balance_issue(progress, wave, ++done);
+      stats_half<D, NP, 0, kOnlyB>(qs, ka, kb, q, p0, p1, sm, ss, a.c);
+      stats_update(p1, a.c, sm[NP - 1], ss[NP - 1]);
+    } else {
+      asm volatile("" : "+v"(sm[NP - 1]));  // keeps the branches' common first terms out of registers before them
+      stats_half<D, NP, 1, kOnlyA>(qs, ka, kb, q, p0, p1, sm, ss, a.c);
+      stats_update(p0, a.c, sm[NB - 1], ss[NB - 1]);
+    }
   }
   __builtin_amdgcn_s_setprio(0);
-  stats_update(p0, a.c, sm[NB - 2], ss[NB - 2]);
-  stats_update(p1, a.c, sm[NB - 1], ss[NB - 1]);
   if (ntok > 32 * nfull && wave == nfull % kGuideWaves) {
     dma_subtile<D>(kchunk, 32 * nfull, ntok, kbuf);
     wait_copies();
-    read_kfrag<D>(kbuf, kf);
-    stats_tail<D, NP>(qs, kf, ntok - 32 * nfull, sm, ss, a.c);
+    read_kfrag<D>(kbuf, ka);
+    stats_tail<D, NP>(qs, ka, ntok - 32 * nfull, sm, ss, a.c);
   }
 
   // merge the half-waves (same rows, other tokens), then the waves, through LDS (the query
@@ -543,28 +609,32 @@ __device__ inline void attn_flush(float part, float* raw_out, int tok0, int ntok
   if (tok0 >= 0 && lane < 32 && tok < ntok) raw_out[tok] = v;
 }
 
-// One sub-tile of pass 2, pipelined like pass 1.  `part` carries the partial row sum of the
-// sub-tile whose pairs are in the vector stage; it is flushed (for the sub-tile starting at
-// token `prev_tok0`) when that sub-tile's last pair has been added.
-template <int D, int NP>
-__device__ inline void attn_steps(const char* qs, const float* lz_s, const Frag (&kf)[Cfg<D>::kSteps],
-                                  Frag (&qa)[Cfg<D>::kSteps], Frag (&qb)[Cfg<D>::kSteps], f32x16& p0, f32x16& p1,
-                                  float& part, int prev_tok0, float* raw_out, int ntok, float c) {
-  using C = Cfg<D>;
+// Half a revolution of pass 2, pipelined like pass 1.  `parta` and `partb` carry the partial row
+// sums of tiles a and b.  The tile that entered with this half (a for H = 0, b for H = 1) has
+// replaced one whose last row block is summed in the half's first step, which then stores that
+// tile's tokens (from chunk token `prev` on).  z holds the start values of the next row block.
+template <int D, int NP, int H, int TILES>
+__device__ inline void attn_half(const char* qs, const float* lz_s, const Frag (&ka)[Cfg<D>::kSteps],
+                                 const Frag (&kb)[Cfg<D>::kSteps], Frag (&q)[Cfg<D>::kSteps], f32x16& z, f32x16& p0,
+                                 f32x16& p1, float& parta, float& partb, int prev, float* raw_out, int ntok, float c) {
+  constexpr int KS = Cfg<D>::kSteps;
+  constexpr int NM = TILES == kBothTiles ? 2 * KS : KS;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     f32x16 n0, n1;
-    read_lz(lz_s, 2 * p, n0);
-    read_lz(lz_s, 2 * p + 1, n1);
-    mfma_pair<C::kSteps, true, true>(qa, qb, kf, n0, n1);
-    const int pn = p + 1 < NP ? p + 1 : 0;
-    read_qfrag<D>(qs, 2 * pn, qa);
-    read_qfrag<D>(qs, 2 * pn + 1, qb);
-    part += attn_sum(p0, c) + attn_sum(p1, c);
-    pin(part, part, part, part);
-    step_schedule<8, 8, 4, 2 * C::kSteps, 2 * C::kSteps, 56 / (2 * C::kSteps), 28 / (2 * C::kSteps)>();
+    read_qfrag<D, KS - kLateQ, KS>(qs, H * NP + p, q);
+    mfma_tiles<KS, true, TILES>(q, ka, kb, z, n0, n1);
+    const int rn = (H * NP + p + 1) % (2 * NP);
+    read_qfrag<D, 0, KS - kLateQ>(qs, rn, q);
+    read_lz(lz_s, rn, z);
+    parta += attn_sum(p0, c);
+    partb += attn_sum(p1, c);
+    pin(parta, partb, parta, partb);
+    // 2 x (16 multiplies + 15 adds) + 2 adds; 32 exp2
+    step_schedule<KS, NM, 64 / NM, 32 / NM, true>();
     if (p == 0) {
-      attn_flush(part, raw_out, prev_tok0, ntok);
+      float& part = H == 0 ? parta : partb;
+      attn_flush(part, raw_out, prev, ntok);
       part = 0.f;
     }
     p0 = n0;
@@ -583,6 +653,7 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_attn(GuideArgs a) {
   __shared__ __attribute__((aligned(16))) float lz_s[NB * 32];
   const int wave = uniform(threadIdx.x >> 6);
   char* kbuf = kst + wave * C::kStageBytes;
+  const uint32_t kbuf_lds = (uint32_t)uniform((int)(uintptr_t)(__attribute__((address_space(3))) char*)kbuf);
   const int64_t tok0 = (int64_t)w.seg * a.n_tot + w.n0 + w.c0;  // first token row of the chunk
   const char* kchunk = (const char*)(a.k + tok0 * D);
   const int ntok = (int)(w.c1 - w.c0);
@@ -595,29 +666,56 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_attn(GuideArgs a) {
   __syncthreads();
 
   float* raw_out = a.raw + ((int64_t)w.rg * a.L * a.Hkv + w.seg) * a.n_tot + w.n0 + w.c0;
-  Frag kf[C::kSteps], qa[C::kSteps], qb[C::kSteps];
-  f32x16 p0, p1;
+  Frag ka[C::kSteps], kb[C::kSteps], q[C::kSteps];
+  f32x16 p0, p1, z;
 #pragma unroll
   for (int i = 0; i < 16; ++i) p0[i] = p1[i] = -INFINITY;  // empty pipeline slot: sums to 0
-  float part = 0.f;
-  int prev = -1;  // first chunk token of the sub-tile in the vector stage (none yet)
-  read_qfrag<D>(qs, 0, qa);
-  read_qfrag<D>(qs, 1, qb);
+  float parta = 0.f, partb = 0.f;
+  int preva = -1, prevb = -1;  // first chunk token of the tile held in a and b (none yet)
+  read_qfrag<D, 0, C::kSteps - kLateQ>(qs, 0, q);
+  read_lz(lz_s, 0, z);
   __shared__ int progress[kGuideWaves];
   if (threadIdx.x < kGuideWaves) progress[threadIdx.x] = 0;
   __syncthreads();
-  for (int done = 0; st < nsub; st += kGuideWaves) {
+  int done = 0;
+  const auto next_tile = [&](Frag(&kf)[C::kSteps]) {
     wait_copies();
     read_kfrag<D>(kbuf, kf);
     wait_lds_reads();
-    if (st + kGuideWaves < nsub) dma_subtile<D>(kchunk, 32 * (st + kGuideWaves), ntok, kbuf);
-    attn_steps<D, NP>(qs, lz_s, kf, qa, qb, p0, p1, part, prev, raw_out, ntok, a.c);
-    prev = 32 * st;
+    st += kGuideWaves;
+    if (32 * (st + 1) <= ntok)
+      dma_whole<D>(kchunk, 32 * st, kbuf_lds);
+    else if (st < nsub)
+      dma_subtile<D>(kchunk, 32 * st, ntok, kbuf);
+    __builtin_amdgcn_sched_barrier(0);  // the step's LDS slots are for the query fragments
+  };
+  if (st < nsub) {
+    next_tile(ka);
+    attn_half<D, NP, 0, kOnlyA>(qs, lz_s, ka, kb, q, z, p0, p1, parta, partb, preva, raw_out, ntok, a.c);
+    preva = 32 * (st - kGuideWaves);
     balance_issue(progress, wave, ++done);
+    while (st + kGuideWaves < nsub) {  // two more tiles
+      next_tile(kb);
+      attn_half<D, NP, 1, kBothTiles>(qs, lz_s, ka, kb, q, z, p0, p1, parta, partb, prevb, raw_out, ntok, a.c);
+      prevb = 32 * (st - kGuideWaves);
+      balance_issue(progress, wave, ++done);
+      next_tile(ka);
+      attn_half<D, NP, 0, kBothTiles>(qs, lz_s, ka, kb, q, z, p0, p1, parta, partb, preva, raw_out, ntok, a.c);
+      preva = 32 * (st - kGuideWaves);
+      balance_issue(progress, wave, ++done);
+    }
+    if (st < nsub) {
+      next_tile(kb);
+      attn_half<D, NP, 1, kBothTiles>(qs, lz_s, ka, kb, q, z, p0, p1, parta, partb, prevb, raw_out, ntok, a.c);
+      prevb = 32 * (st - kGuideWaves);
+      balance_issue(progress, wave, ++done);
+      attn_half<D, NP, 0, kOnlyB>(qs, lz_s, ka, kb, q, z, p0, p1, parta, partb, preva, raw_out, ntok, a.c);
+      attn_flush(partb + attn_sum(p1, a.c), raw_out, prevb, ntok);
+    } else {
+      attn_half<D, NP, 1, kOnlyA>(qs, lz_s, ka, kb, q, z, p0, p1, parta, partb, prevb, raw_out, ntok, a.c);
+      attn_flush(parta + attn_sum(p0, a.c), raw_out, preva, ntok);
+    }
   }
-  __builtin_amdgcn_s_setprio(0);
-  part += attn_sum(p0, a.c) + attn_sum(p1, a.c);
-  attn_flush(part, raw_out, prev, ntok);
 }
 
 // ---------------------------------------------------------------------------- pooling

@@ -20,6 +20,10 @@ pytestmark = pytest.mark.gpu
 CHUNK_CASES = [
     ("unit-edges", 1, 8, 2, 128, [255, 256, 257, 511, 513, 1], [16, 3, 64, 9, 33, 1], synth.DIST_NORMAL, 5),
     ("even-cuts", 1, 8, 2, 64, [4097, 2333, 7681], [16, 80, 40], synth.DIST_STUDENT_T3, 3),
+    # one chunk per sequence: 0 to 9 sub-tiles per wave, so each way in and out of the two-tile loop,
+    # for every number of row blocks, with and without a ragged last sub-tile
+    ("tile-counts", 1, 8, 2, 128, [33, 800, 1030, 1290, 1600, 2085], [16, 33, 48, 64, 20, 5], synth.DIST_STUDENT_T3, 5),
+    ("tile-counts-64", 1, 8, 2, 64, [2070, 31, 1536, 1056, 511, 768], [64, 48, 16, 33, 20, 5], synth.DIST_NORMAL, 1),
     ("merge-kernel", 14, 32, 8, 64, [513, 70, 300], [64, 130, 5], synth.DIST_NORMAL, 5),  # > 768 workgroups
 ]
 
