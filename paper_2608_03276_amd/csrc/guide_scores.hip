@@ -720,10 +720,15 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_attn(GuideArgs a) {
 
 // ---------------------------------------------------------------------------- pooling
 // s_key = (1/(R K)) * sum over the window of the raw sums of all row groups (zero outside the
-// sequence).  A block stages kPoolTile + 2*half raw values (summed over row groups) in LDS
+// sequence).  A block stages TILE + 2*half raw values (summed over row groups) in LDS
 // with coalesced loads, then each thread sums its windows from LDS; windows wider than
 // kPoolMaxHalf use the direct loop.
-constexpr int kPoolTile = 4096;
+constexpr int kPoolTile = 4096;      // calls of many tiles, bound by bytes
+// Calls whose 4096-token tiles leave CUs idle are bound by one block's latency (four rounds of loads
+// and sixteen windows a thread): 24 segments of up to 4097 tokens, the whole sequence of separate
+// calls 76.2 -> 68.8 us.  The line is one block per CU.
+constexpr int kPoolTileFew = 1024;
+constexpr int kPoolFewBlocks = 256;
 constexpr int kPoolMaxHalf = 512;
 
 __device__ inline float raw_at(const GuideArgs& a, const float* raw, int nrg, int64_t j) {
@@ -733,12 +738,13 @@ __device__ inline float raw_at(const GuideArgs& a, const float* raw, int nrg, in
   return v;
 }
 
+template <int TILE>
 __global__ __launch_bounds__(256) void k_guide_pool(GuideArgs a) {
-  __shared__ float buf[kPoolTile + 2 * kPoolMaxHalf];
+  __shared__ float buf[TILE + 2 * kPoolMaxHalf];
   const int seg = blockIdx.y, b = blockIdx.z;
   const int64_t n0 = a.bt.ctx_off[b];
   const int64_t nb = a.bt.ctx_off[b + 1] - n0;
-  const int64_t i0 = (int64_t)blockIdx.x * kPoolTile;
+  const int64_t i0 = (int64_t)blockIdx.x * TILE;
   if (i0 >= nb) return;
   const int gb = (int)(a.bt.g_off[b + 1] - a.bt.g_off[b]);
   const int nrg = (a.R * gb + kRowsPerGroup - 1) / kRowsPerGroup;
@@ -746,7 +752,7 @@ __global__ __launch_bounds__(256) void k_guide_pool(GuideArgs a) {
   float* out = a.s_key + (int64_t)seg * a.n_tot + n0;
   const int half = a.pool_half;
   if (half > kPoolMaxHalf) {  // wide windows: direct sums
-    for (int u = 0; u < kPoolTile / 256; ++u) {
+    for (int u = 0; u < TILE / 256; ++u) {
       const int64_t i = i0 + threadIdx.x + 256 * u;
       if (i >= nb) break;
       float acc = 0.f;
@@ -756,7 +762,7 @@ __global__ __launch_bounds__(256) void k_guide_pool(GuideArgs a) {
     }
     return;
   }
-  const int nstage = kPoolTile + 2 * half;
+  const int nstage = TILE + 2 * half;
   for (int t0 = 0; t0 < nstage; t0 += 256 * 8) {  // eight loads in flight per thread
     float v[8];
 #pragma unroll
@@ -773,7 +779,7 @@ __global__ __launch_bounds__(256) void k_guide_pool(GuideArgs a) {
   }
   __syncthreads();
 #pragma unroll
-  for (int u = 0; u < kPoolTile / 256; ++u) {
+  for (int u = 0; u < TILE / 256; ++u) {
     const int l = threadIdx.x + 256 * u;
     if (i0 + l >= nb) break;
     float acc = 0.f;
@@ -857,8 +863,14 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
     }
   }
   if (a.skip_pool) return hipSuccess;  // the split selection pools the raw sums itself
-  const dim3 pgrid((unsigned)((max_nb + kPoolTile - 1) / kPoolTile), (unsigned)(a.L * a.Hkv), (unsigned)a.bt.batch);
-  hipLaunchKernelGGL(k_guide_pool, pgrid, dim3(256), 0, stream, a);
+  const auto pgrid = [&](int tile) {
+    return dim3((unsigned)((max_nb + tile - 1) / tile), (unsigned)(a.L * a.Hkv), (unsigned)a.bt.batch);
+  };
+  const dim3 wide = pgrid(kPoolTile);
+  if ((int64_t)wide.x * wide.y * wide.z < kPoolFewBlocks)
+    hipLaunchKernelGGL(k_guide_pool<kPoolTileFew>, pgrid(kPoolTileFew), dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(k_guide_pool<kPoolTile>, wide, dim3(256), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && ev && ev[3]) e = hipEventRecord(ev[3], stream);
   return e;
