@@ -7,12 +7,13 @@
 // how many keys equal to T are needed (ties go to the lower index); an ordered compaction then
 // emits, in ascending token order, every index with key > T plus the first `need` indices with
 // key == T: its output slot is #(key > T before i) + min(#(key == T before i), need).
-// Segments of up to 65536 tokens are selected by one workgroup each, whose registers hold
+// Segments of up to 65536 tokens (few of them: 57344) are selected by one workgroup each, whose registers hold
 // every key (k_sel_one: one launch); longer ones by several workgroups over five launches (the
 // split selection below).  Only integer LDS atomics (histogram counts) are used, so the result
 // is deterministic.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "tp_internal.h"
 
@@ -168,27 +169,35 @@ __device__ inline float lane_neighbour(float x, float edge) {
                                                                SHR ? 0x138 : 0x130, 0xF, 0xF, false));
 }
 
-// All threads: the digit of the krem-th largest key among the histogram's nbins (highest first)
-// and how many keys of that digit are still needed, into sel (read after the next barrier).
-template <int NT>
-__device__ inline void pick_digit_block(const uint32_t* hist, int nbins, uint32_t krem, uint32_t* sel, uint32_t* sh) {
-  const int per = nbins >= NT ? nbins / NT : 1;  // digits per thread, from the top
-  const int top = nbins - 1 - per * (int)threadIdx.x;
-  uint32_t sum = 0;
-  if (top >= 0)
-    for (int e = 0; e < per; ++e) sum += hist[top - e];
+// All threads: the digit of the krem-th largest key among the histogram's NBINS (highest first)
+// and how many keys of that digit are still needed, into sel (read after the next barrier).  A
+// digit's count is spread over COPIES adjacent words.
+template <int NT, int NBINS, int COPIES>
+__device__ inline void pick_digit_block(const uint32_t* hist, uint32_t krem, uint32_t* sel, uint32_t* sh) {
+  constexpr int PER = NBINS >= NT ? NBINS / NT : 1;  // digits per thread, from the top
+  const int top = NBINS - 1 - PER * (int)threadIdx.x;
+  const bool in = NBINS >= NT || top >= 0;
+  uint32_t cnt[PER], sum = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    cnt[e] = 0;
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) cnt[e] += in ? hist[(top - e) * COPIES + c] : 0u;
+    sum += cnt[e];
+  }
   uint32_t total;
   uint32_t cum = block_scan<NT / 64>(sum, sh, total);
-  if (top >= 0 && cum < krem && krem <= cum + sum) {
-    for (int e = 0; e < per; ++e) {
-      const uint32_t c = hist[top - e];
-      if (cum + c >= krem) {
-        sel[0] = (uint32_t)(top - e);
-        sel[1] = krem - cum;
-        break;
-      }
-      cum += c;
+  if (cum < krem && krem <= cum + sum) {
+    uint32_t digit = 0, above = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const bool hit = cum < krem && krem <= cum + cnt[e];
+      digit = hit ? (uint32_t)(top - e) : digit;
+      above = hit ? cum : above;
+      cum += cnt[e];
     }
+    sel[0] = digit;
+    sel[1] = krem - above;
   }
 }
 
@@ -206,7 +215,11 @@ __global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segm
   const uint32_t k = (uint32_t)a.k[b];
   const int64_t base = (int64_t)seg * a.n_tot + n0;
   const int a0 = (int)(base & 3);
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
+  // The scores' top digits crowd into some fifty bins, and lanes of a wave that add to one word wait
+  // for each other: lane l adds to copy l % HC.  Worth the longer clearing and summing from 32
+  // keys per thread on (8 segments of 32768 tokens 23.4 -> 21.9 us, of 16384 13.4 -> 13.8).
+  constexpr int HC = G >= 8 ? 4 : 1;
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kBins * HC];
   __shared__ uint32_t scan_sh[NW + 1];
   __shared__ double dred[NW][2];
   __shared__ uint32_t sel[2];
@@ -228,7 +241,7 @@ __global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segm
     // the norms come first; the sweep below reads the same values again (from L2)
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll 1
-    for (int g = 0; g < G; g += GB) {
+    for (int g = 0; g < G && 4 * NT * g < n + a0; g += GB) {
       float4 x[GB], y[GB];
 #pragma unroll
       for (int e = 0; e < GB; ++e) {
@@ -260,11 +273,18 @@ __global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segm
     norm_b = inverse_norm(t2);
   }
 
-  for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+#pragma unroll
+  for (int i = 0; i < kBins * HC / 4; i += NT) ((uint4*)hist)[i + tid] = make_uint4(0, 0, 0, 0);
   __syncthreads();
   uint32_t key[4 * G];
+  const int ng = (n + a0 + 4 * NT - 1) / (4 * NT);  // groups with tokens of this sequence (a batch mixes lengths)
 #pragma unroll
   for (int gb = 0; gb < G; gb += GB) {
+    if (gb >= ng) {
+#pragma unroll
+      for (int i = 0; i < 4 * GB; ++i) key[4 * gb + i] = 0;
+      continue;
+    }
     float4 x[GB], y[GB], edge[GB];
 #pragma unroll
     for (int e = 0; e < GB; ++e) {
@@ -318,37 +338,40 @@ __global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segm
         // 0 marks a slot without a token; no key of a token is 0 (only a NaN's could be)
         const uint32_t ky = t + j >= 0 && t + j < n ? max(order_key(S[j]), 1u) : 0u;
         key[4 * (gb + e) + j] = ky;
-        if (ky != 0) atomicAdd(&hist[ky >> (32 - kTopBits)], 1u);
+        if (ky != 0) atomicAdd(&hist[(ky >> (32 - kTopBits)) * HC + (lane & (HC - 1))], 1u);
       }
       store4(sb, t, n, S);
     }
     __builtin_amdgcn_sched_barrier(0);  // later groups' loads would spill the keys
   }
   __syncthreads();
-  pick_digit_block<NT>(hist, kBins, k, sel, scan_sh);
+  pick_digit_block<NT, kBins, HC>(hist, k, sel, scan_sh);
   __syncthreads();
   uint32_t prefix = sel[0], krem = sel[1];
   // the two remaining digits: bits 19..8 (12 bits), then bits 7..0 (8 bits)
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int shift = pass == 0 ? 8 : 0, bits = pass == 0 ? 12 : 8;
-    for (int i = tid; i < (1 << bits); i += NT) hist[i] = 0;
+  const auto digit = [&](auto bits_c, auto shift_c) {
+    constexpr int bits = decltype(bits_c)::value, shift = decltype(shift_c)::value;
+    for (int i = tid; i < (1 << bits) / 4; i += NT) ((uint4*)hist)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4 * G; ++i) {
+      if (i % (4 * GB) == 0 && i / 4 >= ng) break;
       if ((key[i] >> (shift + bits)) == prefix && key[i] != 0)
         atomicAdd(&hist[(key[i] >> shift) & ((1u << bits) - 1u)], 1u);
     }
     __syncthreads();
-    pick_digit_block<NT>(hist, 1 << bits, krem, sel, scan_sh);
+    pick_digit_block<NT, (1 << bits), 1>(hist, krem, sel, scan_sh);
     __syncthreads();
     prefix = (prefix << bits) | sel[0];
     krem = sel[1];
-  }
+  };
+  digit(std::integral_constant<int, 12>{}, std::integral_constant<int, 8>{});
+  digit(std::integral_constant<int, 8>{}, std::integral_constant<int, 0>{});
   const uint32_t T = prefix, need = krem;
   // keys > T and == T of each wave's 256 consecutive tokens per group, then their running sums
 #pragma unroll
   for (int g = 0; g < G; ++g) {
+    if (g % GB == 0 && g >= ng) break;
     uint32_t gt = 0, eq = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -363,7 +386,7 @@ __global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segm
     uint32_t gs = 0, es = 0;
 #pragma unroll
     for (int e = 0; e < per; ++e)
-      if (lane * per + e < G * NW) {
+      if (lane * per + e < ng * NW) {
         const uint2 c = tab[lane * per + e];
         gs += c.x;
         es += c.y;
@@ -381,7 +404,7 @@ __global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segm
     ei -= es;
 #pragma unroll
     for (int e = 0; e < per; ++e)
-      if (lane * per + e < G * NW) {
+      if (lane * per + e < ng * NW) {
         const uint2 c = tab[lane * per + e];
         tab[lane * per + e] = make_uint2(gi, ei);
         gi += c.x;
@@ -389,14 +412,20 @@ __global__ __launch_bounds__(NT) void k_sel_one(SelectArgs a, int seg0, int segm
       }
   }
   __syncthreads();
+  // taken for a new value, so the comparisons are made again instead of keeping the masks of all
+  // groups above (16 G scalar registers, spilled); with the groups a sequence does not reach left out,
+  // a ragged batch of 8 (256 segments each of 5336 to 65082 tokens) 405 -> 267 us
+  uint32_t T2 = T;
+  asm volatile("" : "+v"(T2));
   int32_t* out = a.kept + (int64_t)seg * a.k_tot + a.kept_off[b];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
+    if (g % GB == 0 && g >= ng) break;
     const int t = tok_of(g);
     uint32_t gm = 0, em = 0, gb = 0, eb = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const bool gt = key[4 * g + j] > T, eq = key[4 * g + j] == T;
+      const bool gt = key[4 * g + j] > T2, eq = key[4 * g + j] == T2;
       gm |= gt ? 1u << j : 0u;
       em |= eq ? 1u << j : 0u;
       gb += lanes_below(__builtin_amdgcn_ballot_w64(gt));
@@ -1027,13 +1056,13 @@ SelectWorkspace select_workspace_layout(int64_t segments, const int64_t* ctx_off
 }
 
 // k_sel_one's rule: every segment's tokens, with the up to 3 slots that its misalignment costs,
-// fit one workgroup's registers, and a pooling window spans adjacent lanes only.  Up to 32768
-// tokens the one launch beats the split's five whatever the number of segments (us for the
-// whole selection, split against one: 8 segments of 8192 tokens 38.0 / 10.0, 8 of 32768 39.6 /
-// 24.1, 256 of 32768 64.7 / 34.9); up to 65536 only where the segments fill part of the chip
-// (8 segments 40.3 / 38.9, 64 49.5 / 49.4, 256 102 / 65.8, 300
-// 124 / 111).  Normalised-add against the former one-workgroup kernel, which read the scores
-// from memory four times: 32 of 32768 60.6 -> 29.7, 256 of 65536 120 -> 83.
+// fit one workgroup's registers, and a pooling window spans adjacent lanes only.  The one launch
+// beats the split's five (us for the whole selection, split against one: 8 segments of 8192 tokens
+// 38.0 / 9.0, 8 of 32768 39.6 / 21.8, 256 of 32768 64.7 / 33.1, 8 of 40000 34.4 / 29.6, 32 of 60000
+// 39.4 / 38.2, 64 of 65536 48.7 / 42.0, 256 of 65536 102 / 58.3) but for few segments near the top
+// of its range, whose one workgroup each takes longer (8 of 65536 36.1 / 38.3, 1 33.1 / 37.7).
+// Normalised-add against the former one-workgroup kernel, which read the scores
+// from memory four times: 32 of 32768 60.6 -> 27.3, 256 of 65536 120 -> 83.
 static int one_span(const SelectArgs& a, int segments) {
   if (a.raw != nullptr && a.pool_half > kOneHalfMax) return 0;
   int64_t most = 0;
@@ -1043,7 +1072,7 @@ static int one_span(const SelectArgs& a, int segments) {
     aligned = aligned && (a.bt.ctx_off[b] & 3) == 0;
   }
   if (!aligned) most += 3;
-  if (most > 32768 && (int64_t)segments * a.bt.batch < 96) return 0;
+  if (most > 57344 && (int64_t)segments * a.bt.batch < 32) return 0;
   return most <= 65536 ? (int)most : 0;
 }
 
@@ -1062,7 +1091,12 @@ hipError_t launch_select_score(const SelectArgs& a, int seg_begin, int seg_end, 
   if (seg_end <= seg_begin) return hipSuccess;
   const int span = one_span(a, segments);
   if (span > 0) {  // the whole selection of these segments
-    if (span <= 4096)
+    // short segments: more threads shorten every phase (256 segments of 4096 tokens 12.2 -> 8.0 us)
+    // while each has a CU to itself; beyond, more segments at once are worth more (512 of 4096:
+    // 13.7 with 256 threads, 14.2 with 1024; 2048 of 2000 24 and 48)
+    if (span <= 4096 && (int64_t)(seg_end - seg_begin) * a.bt.batch <= 256)
+      launch_one<1024, 1>(a, seg_begin, seg_end, segments, stream);
+    else if (span <= 4096)
       launch_one<256, 4>(a, seg_begin, seg_end, segments, stream);
     else if (span <= 8192)
       launch_one<1024, 2>(a, seg_begin, seg_end, segments, stream);

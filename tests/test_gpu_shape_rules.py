@@ -61,9 +61,9 @@ def _select(rng, L, Hkv, lens, rule, ratio, budget, ties):
 
 
 # Each size class of the one-workgroup selection at its last aligned and first unaligned length
-# and one past it, and the split selection beyond 65536 tokens.
-SELECT_LENS = [[4096], [4093, 3], [4094, 3], [8192], [8190, 2, 7], [16384], [16381, 1], [32768], [32767, 5], [65536],
-               [65533, 1], [65534, 6], [65537], [100003, 70000, 1]]
+# and one past it, and the split selection beyond (from 57345 tokens in these calls of few segments).
+SELECT_LENS = [[4096], [4093, 3], [4094, 3], [8192], [8190, 2, 7], [16384], [16381, 1], [32768], [32767, 5], [57344], [57345],
+               [57341, 1], [65536], [65533, 1], [65534, 6], [65537], [100003, 70000, 1]]
 
 
 @pytest.mark.parametrize("rule", [0, 1, 2, 3])
@@ -72,6 +72,18 @@ def test_select_size_classes(gpu_lib, lens, rule):
     rng = np.random.default_rng(71 + rule)
     _select(rng, 1, 3, lens, rule, 0.13, 0, 0)
     _select(rng, 1, 2, lens, rule, 0.0, 777, 5)  # five levels: ties at the threshold
+
+
+@pytest.mark.parametrize("layers", [16, 17])  # 256 short segments, and just beyond: workgroups of 1024 threads, of 256
+def test_select_many_short_segments(gpu_lib, layers):
+    _select(np.random.default_rng(77), layers, 8, [290, 1031], 0, 0.13, 0, 5)
+
+
+@pytest.mark.parametrize("lens", [[65536], [65533, 9], [300, 40001]], ids=lambda v: "-".join(map(str, v)))
+def test_select_many_long_segments(gpu_lib, lens):
+    """32 segments and more keep the one-workgroup selection up to its last length, and skip the
+    register groups that the batch's short sequences do not reach."""
+    _select(np.random.default_rng(78), 4, 8, lens, 0, 0.2, 0, 0)
 
 
 @pytest.mark.parametrize("lens", [[900], [4099, 3000], [20000, 33], [65530, 9], [66000, 12000]],
