@@ -446,12 +446,17 @@ __global__ __launch_bounds__(kGuideThreads, 1) void k_guide_stats(GuideArgs a) {
 // ---------------------------------------------------------------------------- guide keys
 // With the guide's own keys (the paper-literal slice of the causal attention over context +
 // appended guide, Sec. 3.2), guide row j's normaliser also takes the logits of guide keys
-// 0..j.  One workgroup takes up to 256 guide rows of a (sequence, layer, KV head); the
-// guide keys of that head are staged in LDS kGuideKeyTile at a time, and every lane (one
-// row each, its query in registers) walks the keys in the same order, so all lanes read the
-// same key row at once (an LDS broadcast).  The row's (max, sum) over its keys t <= j goes
-// to the extra statistics slot nchunk_max, which the merge below treats as one more chunk.
+// 0..j.  One workgroup takes up to kKeyRows guide rows of a (sequence, layer, KV head); the
+// guide keys of that head are staged in LDS kGuideKeyTile at a time, and kKeyLanes adjacent
+// lanes per row (its query in the registers of each) take every kKeyLanes-th key, so a wave reads
+// kKeyLanes key rows at once (broadcasts from different banks: rows are padded by 16 bytes).
+// The row's (max, sum) over its keys t <= j goes to the extra statistics slot nchunk_max,
+// which the merge below treats as one more chunk.  Bound by a lane's serial chain over its
+// keys: with one lane per row the separate calls on 24 segments of 7 to 33 guide tokens took
+// 68.6 us, with four 62.7.
 constexpr int kGuideKeyTile = 64;
+constexpr int kKeyLanes = 4;
+constexpr int kKeyRows = 256 / kKeyLanes;
 
 template <int D>
 __global__ __launch_bounds__(256) void k_guide_key_stats(GuideArgs a) {
@@ -459,13 +464,14 @@ __global__ __launch_bounds__(256) void k_guide_key_stats(GuideArgs a) {
   const int64_t g0 = a.bt.g_off[b];
   const int gb = (int)(a.bt.g_off[b + 1] - g0);
   const int rows = a.R * gb;
-  const int rho = blockIdx.x * 256 + threadIdx.x;  // guide row of the segment: (r, j)
-  if ((int)blockIdx.x * 256 >= rows) return;       // the whole block has no rows
+  const int rho = blockIdx.x * kKeyRows + threadIdx.x / kKeyLanes;  // guide row of the segment: (r, j)
+  const int part = threadIdx.x % kKeyLanes;
+  if ((int)blockIdx.x * kKeyRows >= rows) return;  // the whole block has no rows
   const int64_t l = seg / a.Hkv, h = seg % a.Hkv;
   const bool live = rho < rows;
   const int r = live ? rho / gb : 0, j = live ? rho % gb : -1;
   const int64_t grow = ((l * a.Hq + h * a.R + r) * a.g_tot) + g0 + (live ? j : 0);
-  __shared__ uint4 keys[kGuideKeyTile][D / 8];
+  __shared__ uint4 keys[kGuideKeyTile][D / 8 + 1];
   uint4 qv[D / 8];  // the row's query, bf16 pairs
   {
     const uint4* qrow = (const uint4*)(a.q + grow * D);
@@ -473,8 +479,8 @@ __global__ __launch_bounds__(256) void k_guide_key_stats(GuideArgs a) {
     for (int p = 0; p < D / 8; ++p) qv[p] = qrow[p];
   }
   // the block's rows need keys 0 .. max j; its last row has the largest j unless it wraps
-  const int last = min(rows, (int)(blockIdx.x + 1) * 256) - 1;
-  const int nkeys = ((int)blockIdx.x * 256) / gb == last / gb ? last % gb + 1 : gb;
+  const int last = min(rows, (int)(blockIdx.x + 1) * kKeyRows) - 1;
+  const int nkeys = ((int)blockIdx.x * kKeyRows) / gb == last / gb ? last % gb + 1 : gb;
   const uint4* kg = (const uint4*)(a.kg + ((l * a.Hkv + h) * a.g_tot + g0) * D);
   float m = kNoMax, s = 0.f;
   for (int t0 = 0; t0 < nkeys; t0 += kGuideKeyTile) {
@@ -483,7 +489,7 @@ __global__ __launch_bounds__(256) void k_guide_key_stats(GuideArgs a) {
     for (int i = threadIdx.x; i < nt * (D / 8); i += 256) keys[i / (D / 8)][i % (D / 8)] = kg[(int64_t)(t0 + i / (D / 8)) * (D / 8) + i % (D / 8)];
     __syncthreads();
     const int tend = min(nt, j - t0 + 1);  // keys t0 .. j of this tile (none for idle lanes)
-    for (int t = 0; t < tend; ++t) {
+    for (int t = part; t < tend; t += kKeyLanes) {
       // fp32 dot product of bf16 pairs (v_dot2_f32_bf16), four independent partial sums
       float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -499,7 +505,9 @@ __global__ __launch_bounds__(256) void k_guide_key_stats(GuideArgs a) {
       merge_stats(m, s, ((part[0] + part[1]) + (part[2] + part[3])) * a.c, 1.0f);
     }
   }
-  if (live) a.stats[(int64_t)a.nchunk_max * ((int64_t)a.L * a.Hq * a.g_tot) + grow] = make_float2(m, s);
+#pragma unroll
+  for (int o = 1; o < kKeyLanes; o <<= 1) merge_stats(m, s, __shfl_xor(m, o), __shfl_xor(s, o));
+  if (live && part == 0) a.stats[(int64_t)a.nchunk_max * ((int64_t)a.L * a.Hq * a.g_tot) + grow] = make_float2(m, s);
 }
 
 // ---------------------------------------------------------------------------- lse merge
@@ -849,7 +857,7 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
     if (e != hipSuccess) return e;
     if (pass == 0) {
       if (a.kg != nullptr) {
-        const dim3 kgrid((unsigned)((a.R * max_gb + 255) / 256), (unsigned)(a.L * a.Hkv), (unsigned)a.bt.batch);
+        const dim3 kgrid((unsigned)((a.R * max_gb + kKeyRows - 1) / kKeyRows), (unsigned)(a.L * a.Hkv), (unsigned)a.bt.batch);
         hipLaunchKernelGGL(k_guide_key_stats<D>, kgrid, dim3(256), 0, stream, a);
       }
       if (!a.fold_lse) {
