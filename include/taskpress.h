@@ -301,7 +301,8 @@ tp_status tp_compact_quantize_kv(const tp_dims* dims, const tp_batch* batch, con
  * [6] after the selection, [7] after the compaction; one kernel runs between consecutive
  * events, except that a step which needs no kernel has none: with guide_lse, none from [0] to
  * [2]; in small calls, where score pass 2 merges the row normalisers itself, none between [1]
- * and [2]; where one kernel pools and selects (contexts of up to 65536 tokens), none between
+ * and [2]; where one kernel pools and selects (contexts of up to 65536 tokens, 57344 with
+ * fewer than 32 segments), none between
  * [5] and [6].
  * num_events = 0 (or a NULL profile) records none.
  */
