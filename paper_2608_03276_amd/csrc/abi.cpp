@@ -580,16 +580,20 @@ static tp_status guide_attention(const tp_dims* dims, const tp_batch* batch, con
   a.c = (float)((double)softmax_scale * 1.4426950408889634);
   a.chunk = lay.chunk;
   int64_t max_nb = 0, max_gb = 0;
+  a.wg_off[0] = 0;
   for (int b = 0; b < batch->batch; ++b) {
-    max_nb = std::max<int64_t>(max_nb, batch->ctx_offsets[b + 1] - batch->ctx_offsets[b]);
-    max_gb = std::max<int64_t>(max_gb, batch->guide_offsets[b + 1] - batch->guide_offsets[b]);
+    const int64_t nb = batch->ctx_offsets[b + 1] - batch->ctx_offsets[b];
+    const int64_t gb = batch->guide_offsets[b + 1] - batch->guide_offsets[b];
+    max_nb = std::max(max_nb, nb);
+    max_gb = std::max(max_gb, gb);
+    a.wg_off[b + 1] = a.wg_off[b] + (int64_t)a.L * a.Hkv * (tp::chunks_of<tp::kAttnUnit>(nb, a.chunk) + (k_guide ? 1 : 0)) *
+                                        ((a.R * gb + tp::kRowsPerGroup - 1) / tp::kRowsPerGroup);
   }
-  const int64_t nchunk = (max_nb + a.chunk - 1) / a.chunk;
   const int64_t nrg = (a.R * max_gb + tp::kRowsPerGroup - 1) / tp::kRowsPerGroup;
-  if (nchunk + 1 > 0x7FFFFFFF || (int64_t)batch->batch * nrg > 65535)
-    return fail(TP_ERR_UNSUPPORTED, "context or guide too long for one launch");
-  a.nchunk_max = (int32_t)nchunk;
-  a.nrg_max = (int32_t)nrg;
+  if ((int64_t)batch->batch * nrg > 65535) return fail(TP_ERR_UNSUPPORTED, "context or guide too long for one launch");
+  a.nchunk_max = (int32_t)((max_nb + a.chunk - 1) / a.chunk);
+  const int64_t padded = (int64_t)a.L * a.Hkv * (a.nchunk_max + (k_guide ? 1 : 0)) * batch->batch * nrg;
+  a.nrg_max = padded <= tp::kAttnPaddedWgs ? (int32_t)nrg : 0;
   if (qa) {
     a.scales = qa->scales;
     a.vq = qa->vq;

@@ -234,36 +234,60 @@ struct AttnUnit {
   int gb, rows, row0, nrows, ntok, slot;
 };
 
+// Workgroup -> unit, by one of two grids (attn_grid).
+// Padded (nrg_max > 0): chunk (the guide unit last) x segment x (sequence, row group), each dimension
+// as large as its largest sequence needs; workgroups without work end at once.
+// Compact: each sequence owns a contiguous range of ids (wg_off), its segments varying fastest, then
+// its chunks (the guide unit last, or first where it is longer than a chunk), then row groups.
 __device__ inline bool attn_unit(const AttnArgs& a, AttnUnit& u) {
-  u.b = blockIdx.z / a.nrg_max;
-  u.rg = blockIdx.z % a.nrg_max;
-  u.seg = blockIdx.y;
-  u.chunk = blockIdx.x;
-  u.l = u.seg / a.Hkv;
-  u.h = u.seg % a.Hkv;
+  const bool keys = a.kg != nullptr, padded = a.nrg_max > 0;
+  int b, part = 0;
+  int64_t id = 0;
+  if (padded) {
+    b = blockIdx.z / a.nrg_max;
+    u.rg = blockIdx.z % a.nrg_max;
+    u.seg = blockIdx.y;
+    part = blockIdx.x;
+  } else {
+    id = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (id >= a.wg_off[a.bt.batch]) return false;  // the last grid row's remainder
+    b = 0;
+#pragma unroll
+    for (int step = TP_MAX_BATCH / 2; step > 0; step >>= 1)
+      if (b + step < a.bt.batch && id >= a.wg_off[b + step]) b += step;
+    id -= a.wg_off[b];
+  }
+  u.b = b;
   u.n0 = a.bt.ctx_off[u.b];
   u.nb = a.bt.ctx_off[u.b + 1] - u.n0;
   u.g0 = a.bt.g_off[u.b];
   u.gb = (int)(a.bt.g_off[u.b + 1] - u.g0);
   u.rows = a.R * u.gb;
-  u.row0 = u.rg * kRowsPerGroup;
-  if (u.row0 >= u.rows) return false;
-  u.nrows = u.rows - u.row0 < kRowsPerGroup ? u.rows - u.row0 : kRowsPerGroup;
   const int csize = seq_chunk<kAttnUnit>(u.nb, a.chunk);
-  u.c0 = (int64_t)u.chunk * csize;
-  if (u.c0 < u.nb) {
-    u.guide = false;
-    u.ntok = (int)(u.nb - u.c0 < csize ? u.nb - u.c0 : csize);
-    u.slot = u.chunk;
-    return true;
+  if (padded) {
+    u.chunk = part;
+    u.guide = keys && part == a.nchunk_max;
+    u.c0 = (int64_t)part * csize;
+    if (u.rg * kRowsPerGroup >= u.rows || (!u.guide && u.c0 >= u.nb)) return false;
+  } else {
+    const int nch = (int)(((uint32_t)u.nb + (uint32_t)csize - 1u) / (uint32_t)csize);
+    const bool first = keys && u.gb > csize;
+    const uint32_t per_seg = (uint32_t)(nch + (keys ? 1 : 0)), segs = (uint32_t)(a.L * a.Hkv);
+    const uint64_t unit = (uint64_t)id / segs;
+    u.seg = (int)((uint64_t)id % segs);
+    part = (int)(unit % per_seg);
+    u.rg = (int)(unit / per_seg);
+    u.guide = first ? part == 0 : part == nch;
+    u.chunk = first ? part - 1 : part;
+    u.c0 = (int64_t)u.chunk * csize;
   }
-  if (a.kg != nullptr && u.chunk == a.nchunk_max) {
-    u.guide = true;
-    u.ntok = u.gb;
-    u.slot = a.nchunk_max;
-    return true;
-  }
-  return false;
+  u.l = u.seg / a.Hkv;
+  u.h = u.seg % a.Hkv;
+  u.row0 = u.rg * kRowsPerGroup;
+  u.nrows = u.rows - u.row0 < kRowsPerGroup ? u.rows - u.row0 : kRowsPerGroup;
+  u.ntok = u.guide ? u.gb : (int)(u.nb - u.c0 < csize ? u.nb - u.c0 : csize);
+  u.slot = u.guide ? a.nchunk_max : u.chunk;
+  return true;
 }
 
 // QK: kAttnNoQuant, or the QKind of the codes when the kernel also performs step 2 (Eq. 2)
@@ -602,24 +626,40 @@ void launch_fwd(const AttnArgs& a, dim3 grid, hipStream_t stream) {
 
 }  // namespace
 
-// The call's target chunk: 32768 when every sequence has at least 131072 tokens, else 8192; calls
-// that give it fewer than three rounds of workgroups (the guide units among them) take the chunk
-// with the least estimated time: for 1 to 4 rounds the shortest whose workgroups fit, and its
-// doublings, since every chunk's partial output is written and merged.  The attention with the
-// guide keys, us at 8192 and at the chunk chosen: one layer of 32q/8kv heads, 64 guide tokens, at
-// 17001 tokens 178 -> 47 (576), at 32768 175 -> 58 (1088), at 131072 203 -> 175 (4288); four
-// layers at 32768 195 -> 170 (4736); seven segments of 3924 tokens 92 -> 29 (256).
-int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off,
-                        int32_t batch) {
-  const int64_t R = Hq / Hkv, segs = (int64_t)L * Hkv;
-  bool all_long = true;
+// Bytes of the partial statistics and outputs of `slots` chunks of `rows` guide rows.
+static int64_t partial_bytes(int64_t slots, int64_t rows, int head_dim) {
+  auto up = [](int64_t x) { return (x + 255) / 256 * 256; };
+  return up(slots * rows * (int64_t)sizeof(float2)) + up(slots * rows * head_dim * (int64_t)sizeof(float));
+}
+
+static int32_t usual_attn_chunk(const int64_t* ctx_off, int32_t batch) {
+  for (int b = 0; b < batch; ++b)
+    if (ctx_off[b + 1] - ctx_off[b] < 131072) return 8192;
+  return 32768;
+}
+
+// The call's target chunk: the usual one, 32768 when every sequence has at least 131072 tokens, else
+// 8192; calls that give it fewer than three rounds of workgroups (the guide units among them) take
+// the chunk with the least estimated time, where that is under kAttnPlanGain of the usual one's:
+// for 1 to 4 rounds the shortest whose workgroups fit, and its doublings, since every chunk's
+// partial output is written and merged.  The estimate is rough (rounds of whole units), so a small
+// estimated gain is not taken: over 296 random calls, against the usual chunk, 10 were more than
+// 2 % slower at a line of 0.9 (25.2 -> 27.7 us at worst), 6 at 0.8, both 1.53 times faster in the
+// mean.  Nor are contexts up to kAttnPlanMin tokens cut (311 tokens in chunks of 64 13.6 -> 14.4
+// us) or chunks of under kAttnChunkMin made (no call gained by them).  The attention with the guide keys, us at 8192 and at the
+// chunk chosen: one layer of 32q/8kv heads, 64 guide tokens, at 17001 tokens 178 -> 43 (640), at
+// 32768 175 -> 58 (1088), at 131072 203 -> 175 (4288); seven segments of 3924 tokens 92 -> 29 (256).
+constexpr double kAttnPlanGain = 0.8;
+constexpr int64_t kAttnPlanMin = 384;
+constexpr int kAttnChunkMin = 128;
+
+static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off,
+                               int32_t batch) {
+  const int64_t R = Hq / Hkv, segs = (int64_t)L * Hkv, rows_tot = (int64_t)L * Hq * g_off[batch];
   int64_t longest = 0;
-  for (int b = 0; b < batch; ++b) {
-    longest = std::max(longest, ctx_off[b + 1] - ctx_off[b]);
-    all_long = all_long && ctx_off[b + 1] - ctx_off[b] >= 131072;
-  }
-  const int32_t usual = all_long ? 32768 : 8192;
-  const double row_slots = (double)L * Hq * (double)g_off[batch];
+  for (int b = 0; b < batch; ++b) longest = std::max(longest, ctx_off[b + 1] - ctx_off[b]);
+  const int32_t usual = usual_attn_chunk(ctx_off, batch);
+  if (longest <= kAttnPlanMin) return usual;
   struct Cost {
     double time, rounds;
   };
@@ -633,16 +673,16 @@ int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_o
     }
     const double rounds = ceil(wgs / kAttnCus);
     const double slots = (double)((longest + target - 1) / target);
-    return Cost{rounds * (kAttnWgTokens + (double)most) + slots * (row_slots * kAttnMergeTokens + kAttnSlotTokens),
+    return Cost{rounds * (kAttnWgTokens + (double)most) + slots * ((double)rows_tot * kAttnMergeTokens + kAttnSlotTokens),
                 rounds};
   };
   const Cost at_usual = cost_of(usual);
   if (at_usual.rounds >= 3.0) return usual;
   // for 1, 2, .. rounds of the chip, the shortest chunk whose workgroups fit them
   int32_t best = usual;
-  double least = at_usual.time * 0.97;
+  double least = at_usual.time * kAttnPlanGain;
   for (int r = 1; r <= 4; ++r) {
-    int32_t lo = 1, hi = kChunkWhole / kAttnUnit - 1;  // in units; wgs falls as the chunk grows
+    int32_t lo = kAttnChunkMin / kAttnUnit, hi = kChunkWhole / kAttnUnit - 1;  // in units; wgs falls as the chunk grows
     while (lo < hi) {
       const int32_t mid = (lo + hi) / 2;
       if (cost_of(mid * kAttnUnit).rounds <= r)
@@ -664,18 +704,15 @@ int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_o
 
 AttnWorkspace attn_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_dim, const int64_t* ctx_off,
                                     const int64_t* g_off, int32_t batch) {
-  int64_t max_nb = 0;
-  for (int b = 0; b < batch; ++b)
-    if (ctx_off[b + 1] - ctx_off[b] > max_nb) max_nb = ctx_off[b + 1] - ctx_off[b];
-  const int32_t chunk = plan_attn_chunk(L, Hq, Hkv, ctx_off, g_off, batch);
-  const int64_t nslot = (max_nb + chunk - 1) / chunk + 1;  // the context chunks, then the guide keys
-  const int64_t rows = (int64_t)L * Hq * g_off[batch];
-  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  int64_t longest = 0;
+  for (int b = 0; b < batch; ++b) longest = std::max(longest, ctx_off[b + 1] - ctx_off[b]);
   AttnWorkspace w;
-  w.chunk = chunk;
+  w.chunk = plan_attn_chunk(L, Hq, Hkv, ctx_off, g_off, batch);
+  const int64_t nslot = (longest + w.chunk - 1) / w.chunk + 1;  // the context chunks, then the guide keys
+  const int64_t rows = (int64_t)L * Hq * g_off[batch];
   w.pstat_off = 0;
-  w.po_off = up((size_t)nslot * rows * sizeof(float2));
-  w.total = w.po_off + up((size_t)nslot * rows * head_dim * sizeof(float));
+  w.po_off = ((size_t)nslot * rows * sizeof(float2) + 255) & ~(size_t)255;
+  w.total = (size_t)partial_bytes(nslot, rows, head_dim);
   return w;
 }
 
@@ -683,8 +720,13 @@ hipError_t launch_guide_attention(const AttnArgs& a, int head_dim, hipStream_t s
   int64_t max_gb = 0;
   for (int b = 0; b < a.bt.batch; ++b)
     if (a.bt.g_off[b + 1] - a.bt.g_off[b] > max_gb) max_gb = a.bt.g_off[b + 1] - a.bt.g_off[b];
-  const dim3 grid((unsigned)(a.nchunk_max + (a.kg != nullptr ? 1 : 0)), (unsigned)(a.L * a.Hkv),
-                  (unsigned)(a.bt.batch * a.nrg_max));
+  dim3 grid((unsigned)(a.nchunk_max + (a.kg != nullptr ? 1 : 0)), (unsigned)(a.L * a.Hkv),
+            (unsigned)(a.bt.batch * a.nrg_max));
+  if (a.nrg_max == 0) {
+    constexpr int64_t kGridRow = (int64_t)1 << 22;  // a grid dimension holds fewer than 2^32 work-items
+    const int64_t nwg = a.wg_off[a.bt.batch];
+    grid = dim3((unsigned)std::min(nwg, kGridRow), (unsigned)((nwg + kGridRow - 1) / kGridRow));
+  }
   const dim3 mgrid((unsigned)((a.L * a.Hq * max_gb + 3) / 4), (unsigned)a.bt.batch);
   if (head_dim == 128) {
     launch_fwd<128>(a, grid, stream);

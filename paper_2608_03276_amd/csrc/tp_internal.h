@@ -136,12 +136,16 @@ constexpr unsigned kLeanBlocks = 256;
 hipError_t launch_quantize_lean(const QuantArgs& a, int head_dim, unsigned blocks, hipStream_t stream);
 
 // ---------------------------------------------------------------- guide rows' prefill attention
-// Context tokens per workgroup of the guide rows' attention, for a call: 32768 when every
-// sequence has at least 131072 (fewer partial outputs to merge), else 8192, shorter where that
-// leaves the chip idle; a multiple of kAttnUnit (a pair of 32-token sub-tiles) below 8192.
+// Context tokens per workgroup of the guide rows' attention, for a call (plan_attn_chunk): 32768 when
+// every sequence has at least 131072 (fewer partial outputs to merge), else 8192, shorter where
+// that leaves the chip idle; a multiple of kAttnUnit (a pair of 32-token sub-tiles) below 8192.
 constexpr int kAttnUnit = 64;
-int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off,
-                        int32_t batch);
+// The padded grid (attn_unit) is used up to this many workgroups, two rounds of the chip; beyond, the
+// compact one.  us at the same chunk, padded / compact: 2 layers of 64q/8kv heads at 427 tokens, 146
+// guide tokens (400 workgroups) 33.7 / 38.4, 9 layers of 8q/2kv heads with 5 sequences 38.8 / 41.3;
+// 32 layers of 32q/8kv heads at 32768 (1280) 1287 / 1187, at 131072 (1280) 5170 / 4420, 8 layers of
+// 64q/8kv heads at 2000 tokens, 300 guide tokens (1280) 343 / 282.
+constexpr int64_t kAttnPaddedWgs = 512;
 
 struct AttnArgs {
   const uint16_t* q;   // bf16 [L][Hq][G_tot][d]
@@ -158,8 +162,11 @@ struct AttnArgs {
   float c;             // softmax_scale * log2(e)
   int32_t chunk;       // target context tokens per chunk (plan_attn_chunk of the call)
   int32_t nchunk_max;  // slots of the context chunks: ceil(longest sequence / chunk)
-  int32_t nrg_max;     // row groups of the largest R * G_b
+  int32_t nrg_max;     // row groups of the largest R * G_b; 0: the compact grid
   BatchArgs bt;
+  // the compact grid's first workgroup of each sequence: sequence b has L * Hkv * (its chunks and,
+  // with guide keys, the guide unit) * nrg_b of them
+  int64_t wg_off[TP_MAX_BATCH + 1];
   // Step 2 from the staged V sub-tiles (tp_guide_attention_quantize); vq == nullptr: none.
   float* scales;       // fp32 [L][Hkv][N_tot]
   uint8_t* vq;         // [L][Hkv][N_tot][row_bytes]

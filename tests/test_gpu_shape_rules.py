@@ -139,11 +139,15 @@ def test_evict_overlap_line(gpu_lib, given_lse, full_codes, heads):
             assert torch.equal(getattr(got, name), getattr(ref, name)), name
 
 
-# Attention chunks: multiples of 64 tokens in calls of few workgroups, 8192 from three rounds on.
+# Attention chunks: multiples of 64 tokens in calls of few workgroups, 8192 from three rounds on.  Grids
+# of up to 512 workgroups are padded to the longest sequence and guide, larger ones compact.
 ATTN_CASES = [
     ("unit-edges", 1, 8, 2, 128, [63, 64, 65, 129, 700, 1], [16, 3, 64, 9, 33, 1], True),
     ("even-cuts", 1, 8, 2, 64, [4097, 2333, 7681], [16, 80, 40], True),
     ("many-slots", 1, 2, 1, 128, [12000], [5], False),  # more chunks than the merge loads at once
+    # compact grid: ten to one row groups a sequence, a guide longer than its sequence's chunks (first)
+    ("ragged-compact", 2, 16, 2, 64, [3000, 130, 1200, 65, 2500], [300, 3, 40, 129, 1], True),
+    ("ragged-compact-128", 2, 16, 2, 128, [2100, 64, 700], [40, 150, 1], False),
     ("usual-chunk", 12, 64, 64, 64, [90, 8193], [2, 1], True),  # > 768 workgroups
 ]
 
