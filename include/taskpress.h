@@ -118,6 +118,10 @@ int64_t tp_keep_count(int64_t n, double keep_ratio, int64_t keep_budget);
 /*
  * Bytes of device workspace `fn` needs for these dims / batch (host only).
  * TP_FN_GUIDE_SCORES needs guide_offsets; TP_FN_COMBINE_SELECT_TOPK does not.
+ * For the same dims the size never falls when a sequence or a guide gets longer or a sequence is
+ * added at the end, so a buffer of the longest batch's size serves shorter ones; the one exception is
+ * TP_FN_GUIDE_ATTENTION, which needs less once every sequence has 131072 context tokens (there,
+ * take the larger of that size and the size with one sequence of 131071).
  */
 tp_status tp_workspace_size(int32_t fn, const tp_dims* dims, const tp_batch* batch, size_t* bytes);
 

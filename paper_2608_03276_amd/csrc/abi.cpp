@@ -62,9 +62,9 @@ tp_status check_offsets(const int64_t* off, int32_t batch, const char* what, boo
 // holds fewer than 2^32 work-items per dimension): at most 2^30 context tokens per (layer,
 // head) (the gather launches 4 work-items per kept token; kept indices are int32), at most
 // 2^32 guide rows in all and 2^26 per sequence (the row merges launch a work-item per row and
-// 64 per row), 2^31 - 1 guide tokens, and 2^60 bytes of per-chunk row partials (chunks of
-// 8192 tokens, the smallest any kernel uses).  Far above any cache one GPU holds.  `d` has
-// passed check_dims.
+// 64 per row), 2^31 - 1 guide tokens, and 2^60 bytes of per-chunk row partials in chunks of
+// 8192 tokens (shorter chunks are planned only while their partials fit that or a fixed 136 MB).
+// Far above any cache one GPU holds.  `d` has passed check_dims.
 tp_status check_batch(const tp_dims* d, const tp_batch* bt, bool need_guides) {
   if (!bt) return fail(TP_ERR_NULL, "batch is NULL");
   if (bt->batch < 1) return fail(TP_ERR_SHAPE, "batch must be >= 1");

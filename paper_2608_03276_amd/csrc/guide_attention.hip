@@ -646,15 +646,16 @@ static int32_t usual_attn_chunk(const int64_t* ctx_off, int32_t batch) {
 // estimated gain is not taken: over 296 random calls, against the usual chunk, 10 were more than
 // 2 % slower at a line of 0.9 (25.2 -> 27.7 us at worst), 6 at 0.8, both 1.53 times faster in the
 // mean.  Nor are contexts up to kAttnPlanMin tokens cut (311 tokens in chunks of 64 13.6 -> 14.4
-// us) or chunks of under kAttnChunkMin made (no call gained by them).  The attention with the guide keys, us at 8192 and at the
+// us) or chunks of under kAttnChunkMin made (no call gained by them).  Partials are kept within
+// `budget` bytes, the call's workspace.  The attention with the guide keys, us at 8192 and at the
 // chunk chosen: one layer of 32q/8kv heads, 64 guide tokens, at 17001 tokens 178 -> 43 (640), at
 // 32768 175 -> 58 (1088), at 131072 203 -> 175 (4288); seven segments of 3924 tokens 92 -> 29 (256).
 constexpr double kAttnPlanGain = 0.8;
 constexpr int64_t kAttnPlanMin = 384;
 constexpr int kAttnChunkMin = 128;
 
-static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off,
-                               int32_t batch) {
+static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_dim, const int64_t* ctx_off,
+                               const int64_t* g_off, int32_t batch, int64_t budget) {
   const int64_t R = Hq / Hkv, segs = (int64_t)L * Hkv, rows_tot = (int64_t)L * Hq * g_off[batch];
   int64_t longest = 0;
   for (int b = 0; b < batch; ++b) longest = std::max(longest, ctx_off[b + 1] - ctx_off[b]);
@@ -692,6 +693,7 @@ static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t
     }
     // and longer ones, where merging that many partial outputs would cost more
     for (int32_t target = lo * kAttnUnit; target < kChunkWhole; target *= 2) {
+      if (partial_bytes((longest + target - 1) / target + 1, rows_tot, head_dim) > budget) continue;
       const Cost c = cost_of(target);
       if (c.time < least) {
         best = target;
@@ -702,17 +704,29 @@ static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t
   return best;
 }
 
+// The partials' room: what the usual chunk needs, or, where shorter chunks may be planned, what 1024
+// workgroups of 256 rows write (four rounds of the chip, 136 MB at head_dim 128), at most what
+// kAttnChunkMin needs.  Not the planned chunk's own need, which falls where a longer call takes
+// the usual chunk: one layer of 32q/8kv heads, 64 guide tokens, needs 102 MB at 524288 tokens and
+// 34 MB at 1000000.
+constexpr int64_t kAttnPlanRows = 1024 * 256;
+
 AttnWorkspace attn_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_dim, const int64_t* ctx_off,
                                     const int64_t* g_off, int32_t batch) {
   int64_t longest = 0;
   for (int b = 0; b < batch; ++b) longest = std::max(longest, ctx_off[b + 1] - ctx_off[b]);
-  AttnWorkspace w;
-  w.chunk = plan_attn_chunk(L, Hq, Hkv, ctx_off, g_off, batch);
-  const int64_t nslot = (longest + w.chunk - 1) / w.chunk + 1;  // the context chunks, then the guide keys
   const int64_t rows = (int64_t)L * Hq * g_off[batch];
+  const auto need = [&](int64_t chunk) { return partial_bytes((longest + chunk - 1) / chunk + 1, rows, head_dim); };
+  // need(kAttnChunkMin) itself may not fit 64 bits
+  const int64_t fine = (longest + kAttnChunkMin - 1) / kAttnChunkMin + 1;
+  const int64_t plan = partial_bytes(1, kAttnPlanRows, head_dim);
+  AttnWorkspace w;
+  w.total = (size_t)std::max(need(usual_attn_chunk(ctx_off, batch)),
+                             (double)fine * (double)rows < (double)kAttnPlanRows ? need(kAttnChunkMin) : plan);
+  w.chunk = plan_attn_chunk(L, Hq, Hkv, head_dim, ctx_off, g_off, batch, (int64_t)w.total);
+  const int64_t nslot = (longest + w.chunk - 1) / w.chunk + 1;  // the context chunks, then the guide keys
   w.pstat_off = 0;
   w.po_off = ((size_t)nslot * rows * sizeof(float2) + 255) & ~(size_t)255;
-  w.total = (size_t)partial_bytes(nslot, rows, head_dim);
   return w;
 }
 

@@ -889,7 +889,9 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
 // less.  Both passes together, us at 8192 and at the target chosen: one layer of 32q/8kv heads
 // with 64 guide tokens at 32768 tokens 200 -> 64 (1024), four layers 208 -> 164 (4096), three
 // layers at 131072 tokens 524 -> 505 (4096), seven segments of 3924 tokens 108 -> 33 (256).
-int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off, int32_t batch) {
+// Chunks of which the statistics would exceed `max_slots` are not planned.
+static int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off,
+                          int32_t batch, int64_t max_slots) {
   static const int32_t kTargets[] = {16384, 14336, 12288, 10240, 8192, 7168, 6144, 5120, 4096, 3584, 3072,
                                      2560,  2048,  1792,  1536,  1280, 1024, 768,  512,  256};
   static const double kTokenCost[4] = {0.75, 0.75, 0.8, 1.0};  // by staged row-block pairs: K's bytes bound few rows
@@ -906,7 +908,11 @@ int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, c
     seq[b].rg = (double)((rows + kRowsPerGroup - 1) / kRowsPerGroup);
   }
   bool all_long = true;
-  for (int b = 0; b < batch; ++b) all_long = all_long && seq[b].n >= kLongContext;
+  uint32_t most_n = 0;
+  for (int b = 0; b < batch; ++b) {
+    all_long = all_long && seq[b].n >= kLongContext;
+    most_n = std::max(most_n, seq[b].n);
+  }
   const int32_t usual = all_long ? 16384 : 8192;
   struct Cost {
     double time, rounds;
@@ -935,6 +941,7 @@ int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, c
   int32_t best = usual;
   double least = at_usual.time * 0.97;
   for (const int32_t target : kTargets) {
+    if (((int64_t)most_n + target - 1) / target > max_slots) break;
     const Cost c = cost_of(target);
     if (c.time < least) {
       best = target;
@@ -945,6 +952,12 @@ int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, c
   return best;
 }
 
+// Room for the chunks' statistics: what chunks of 8192 tokens need or, where shorter ones may be
+// planned, what 4352 workgroups of 256 rows write (16 rounds of the chip and a little, 8.9 MB), at
+// most what kChunkUnit needs.  Not the planned chunk's own need, which falls where a longer call
+// takes longer chunks.
+constexpr int64_t kStatsPlanRows = 4352 * 256;
+
 GuideWorkspace guide_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off,
                                       const int64_t* g_off, int32_t batch) {
   int64_t max_nb = 0, max_gb = 0;
@@ -953,16 +966,18 @@ GuideWorkspace guide_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, const 
     if (g_off[b + 1] - g_off[b] > max_gb) max_gb = g_off[b + 1] - g_off[b];
   }
   const int64_t n_tot = ctx_off[batch], g_tot = g_off[batch];
-  const int64_t R = Hq / Hkv;
-  const int32_t chunk = plan_chunk(L, Hq, Hkv, ctx_off, g_off, batch);
-  const int64_t nchunk = (max_nb + chunk - 1) / chunk;
+  const int64_t R = Hq / Hkv, rows = (int64_t)L * Hq * g_tot;
   const int64_t nrg = (R * max_gb + kRowsPerGroup - 1) / kRowsPerGroup;
+  // slots of per-chunk statistics, and one for the guide keys
+  const int64_t whole = (max_nb + kChunkWhole - 1) / kChunkWhole + 1, fine = (max_nb + kChunkUnit - 1) / kChunkUnit + 1;
+  const int64_t entries = std::max(whole * rows, (double)fine * (double)rows < (double)kStatsPlanRows ? fine * rows
+                                                                                                     : kStatsPlanRows);
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   GuideWorkspace w;
-  w.chunk = chunk;
-  w.stats_off = 0;  // nchunk slots of per-chunk statistics, plus one for the guide keys
-  w.lse_off = up((size_t)(nchunk + 1) * L * Hq * g_tot * sizeof(float2));
-  w.raw_off = w.lse_off + up((size_t)L * Hq * g_tot * sizeof(float));
+  w.chunk = plan_chunk(L, Hq, Hkv, ctx_off, g_off, batch, entries / rows - 1);
+  w.stats_off = 0;
+  w.lse_off = up((size_t)entries * sizeof(float2));
+  w.raw_off = w.lse_off + up((size_t)rows * sizeof(float));
   w.total = w.raw_off + up((size_t)nrg * L * Hkv * n_tot * sizeof(float));
   return w;
 }

@@ -21,13 +21,12 @@ struct BatchArgs {
 constexpr int kGuideThreads = 512;       // 8 waves of 64, two per SIMD
 constexpr int kGuideWaves = kGuideThreads / 64;
 constexpr int kRowsPerGroup = 256;       // guide rows handled by one workgroup
-// Context tokens of one segment per score-pass workgroup (a "chunk"): a call's target is at
+// Context tokens of one segment per score-pass workgroup (a "chunk"): a call's target (plan_chunk) is at
 // most 16384 (long chunks spread the query staging and the statistics merge over more tokens)
 // and shorter where those would leave the chip idle or its last round of workgroups nearly
 // empty.  Always a multiple of 256, so every wave of a workgroup gets the same number of
 // 32-token sub-tiles.
 constexpr int kChunkUnit = 256;
-int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off, const int64_t* g_off, int32_t batch);
 
 // Chunk of one sequence of n <= 2^30 tokens under the call's `target`.  Targets from 8192 up (calls of
 // many rounds of workgroups) cut full chunks and a remainder, whose short workgroups fill the
@@ -82,8 +81,10 @@ struct GuideArgs {
 
 struct GuideWorkspace {
   size_t stats_off, lse_off, raw_off, total;
-  int32_t chunk;  // plan_chunk of the call, which the layout follows
+  int32_t chunk;  // plan_chunk of the call, whose statistics fit
 };
+// `total` never falls when a sequence or a guide grows or a sequence is added (same L, Hq, Hkv): a
+// caller may size a buffer once, for its longest batch.
 GuideWorkspace guide_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx_off,
                                       const int64_t* g_off, int32_t batch);
 
@@ -177,8 +178,10 @@ struct AttnArgs {
 
 struct AttnWorkspace {
   size_t pstat_off, po_off, total;
-  int32_t chunk;  // plan_attn_chunk of the call, which the layout follows
+  int32_t chunk;  // plan_attn_chunk of the call, whose partials fit
 };
+// `total` never falls when a sequence or a guide grows or a sequence is added (same L, Hq, Hkv and
+// head_dim), except where every sequence comes to have 131072 tokens (fewer, longer chunks).
 AttnWorkspace attn_workspace_layout(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_dim, const int64_t* ctx_off,
                                     const int64_t* g_off, int32_t batch);
 hipError_t launch_guide_attention(const AttnArgs& a, int head_dim, hipStream_t stream);

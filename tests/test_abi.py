@@ -75,6 +75,48 @@ def _gs(d, bt, q=FAKE, k=FAKE, scale=0.125, pool=5, s=FAKE, ws=FAKE, wsb=1 << 40
 
 
 @no_gpu
+def test_workspace_size_never_falls_with_the_batch():
+    """A buffer sized for the longest batch serves shorter ones of the same dims (the chunks planned
+    for a call must not make a shorter call need more): sizes along growing contexts, guides and
+    batches, over the lengths where the plans change."""
+    def size(fn, d, lens, guides):
+        return B.tp_workspace_size(fn, d, B.Batch(np.concatenate([[0], np.cumsum(lens)]).tolist(),
+                                                  np.concatenate([[0], np.cumsum(guides)]).tolist()))
+
+    fns = [B.TP_FN_GUIDE_SCORES, B.TP_FN_EVICT, B.TP_FN_GUIDE_ATTENTION]
+    lens = sorted({int(x) for e in range(0, 21) for x in (2 ** e - 1, 2 ** e, 2 ** e + 1, 1.4 * 2 ** e) if x >= 1}
+                  | {524288, 1000000})
+    for L, Hq, Hkv, hd in ((1, 32, 8, 128), (1, 8, 2, 64), (4, 32, 8, 128), (32, 32, 8, 128), (48, 16, 2, 128)):
+        d = B.dims(L, Hq, Hkv, hd)
+        for fn in fns:
+            last = last_long = 0
+            for n in lens:
+                now = size(fn, d, [n], [64])
+                if fn == B.TP_FN_GUIDE_ATTENTION and n >= 131072:  # the documented exception
+                    assert now >= last_long, (L, Hq, fn, n)
+                    last_long = now
+                else:
+                    assert now >= last, (L, Hq, fn, n)
+                    last = now
+            last = 0
+            for g in (1, 7, 63, 64, 65, 128, 200, 256):
+                now = size(fn, d, [17001, 900], [g, 3])
+                assert now >= last, (L, Hq, fn, g)
+                last = now
+    rng = np.random.default_rng(19)
+    for _ in range(300):  # any batch against a longer one
+        Hkv = int(rng.choice([1, 2, 8]))
+        d = B.dims(int(rng.integers(1, 33)), Hkv * int(rng.choice([1, 4, 8])), Hkv, int(rng.choice([64, 128])))
+        k = int(rng.integers(1, 9))
+        a = np.exp(rng.uniform(0, np.log(130000), k)).astype(int).clip(1)
+        g = np.exp(rng.uniform(0, np.log(300), k)).astype(int).clip(1)
+        more = (a * np.exp(rng.uniform(0, 1.5, k))).astype(int)
+        longer = np.concatenate([more, [500]])  # 500 keeps the attention's usual chunk
+        gl = np.concatenate([(g * np.exp(rng.uniform(0, 1, k))).astype(int), [9]])
+        for fn in fns:
+            assert size(fn, d, a, g) <= size(fn, d, longer, gl), (fn, d.num_layers, a.tolist(), longer.tolist())
+
+
 def test_guide_scores_validation():
     d = B.dims(2, 8, 2, 64)
     bt = B.Batch([0, 100, 300], [0, 16, 20])
