@@ -75,11 +75,11 @@ def algorithmic_bytes(w, kept_total_per_head, full_codes=True, normalisers_given
         path = LH * (n * (2 * d + 2 * d + 4) + kt * (2 * d + 2 * d + 4 + 2 * d + rb + 4)) + q_bytes
     # tp_evict quantises a part of the V rows (rounded down to 64 rows) on its second stream
     # beside each score pass (two k_quantize_lean launches), or, with the normalisers given,
-    # one part beside the rest of the step (one launch); the k_quantize launch timed between
-    # the events does the rest.  LEAN_PART gives the part as a fraction of the rows.
+    # one part beside pass 2 (one launch); the k_quantize launch timed between the events does the
+    # rest.  lean_part gives the part as a fraction of the rows.
     rows = LH * n
     full = per["k_quantize"]
-    num, den = LEAN_PART[(normalisers_given, full_codes)]
+    num, den = lean_part(w, full_codes, normalisers_given)
     r_lean = rows * num // den // 64 * 64
     launches = LEAN_LAUNCHES[normalisers_given]
     per["k_quantize"] = full * (rows - launches * r_lean) // rows
@@ -100,10 +100,25 @@ def attention_bytes(w, with_step2: bool) -> int:
     return b
 
 
-# k_quantize_lean launches per tp_evict call, without / with the normalisers given, and the
-# rows of each launch as a fraction of all rows, by (normalisers given, full codes)
+# k_quantize_lean launches per tp_evict call, without / with the normalisers given
 LEAN_LAUNCHES = {False: 2, True: 1}
-LEAN_PART = {(False, True): (2, 5), (False, False): (1, 2), (True, True): (1, 2), (True, False): (3, 5)}
+
+
+def lean_part(w, full_codes=True, normalisers_given=False):
+    """Rows of each k_quantize_lean launch as a fraction (numerator, denominator) of all rows: the
+    rule of tp_evict (abi.cpp, step2_split), by the guide rows (multiples of 64) that a context
+    token meets in the mean."""
+    rows = (sum(n * (-(-w.R * g // 64) * 64) for n, g in zip(w.ctx_lens, w.guide_lens)) / w.n_tot
+            if w.d == 128 else float("inf"))
+    if full_codes:
+        if rows <= 192:
+            return (1, 5)
+        if normalisers_given:
+            return (3, 10) if rows <= 256 else (1, 2)
+        return (7, 20) if rows <= 256 else (2, 5)
+    if normalisers_given:
+        return (1, 5) if rows <= 64 else (3, 5)
+    return (3, 10) if rows <= 192 else (1, 2)
 
 
 def source_sha256(kernel: str) -> str:

@@ -332,10 +332,10 @@ typedef struct tp_profile {
  * TP_ERR_NULL), and everything runs on `stream` (no second stream, no library state).
  * workspace: >= tp_workspace_size(TP_FN_EVICT, ...) bytes, 256-byte aligned (the score
  * pass's workspace followed by the selection's).
- * In large calls (V of 640 MB or more; 1 GB with guide_lse) step 2 of most V rows runs on a
- * second stream of the library's: 2/5 concurrently with each score pass (half with each when
- * v_q is NULL), or, with guide_lse given, the last half (3/5 when v_q is NULL) concurrently
- * with score pass 2; smaller calls run everything on `stream`.  The arithmetic is the same, so
+ * In large calls (V of 640 MB or more; 1 GB with guide_lse) step 2 of part of the V rows runs on a
+ * second stream of the library's, a fifth to a half of them concurrently with each score pass, or,
+ * with guide_lse given, the last fifth to three fifths concurrently with score pass 2 (less for
+ * short guides, and where codes are written); smaller calls run everything on `stream`.  The arithmetic is the same, so
  * the results are as for the separate calls.  That stream and four events are created, with
  * default priority, by the first such call on a device and kept until the process ends
  * (TP_ERR_HIP if that fails); the work is forked from and joined back to `stream`, so the call

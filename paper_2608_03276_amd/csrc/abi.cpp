@@ -712,6 +712,49 @@ static bool step2_overlaps(int64_t rows, int32_t head_dim, bool pass1) {
   return rows * head_dim * 2 >= line;
 }
 
+// The part of step 2's rows that the lean kernel takes beside each score pass, and its workgroups
+// beside pass 2.  With pass 1 and codes 2/5 each (the middle fifth runs alone between the
+// passes), or half each when only the scales are written (lighter, so all of it fits beside the
+// passes).  With the normalisers given there is no pass 1: the regular kernel takes the first
+// half (2/5 for scales only) and the lean kernel the rest beside pass 2.  Less where the passes are short for
+// K's bytes, few guide rows at head_dim 128: the lean kernel moves 1.6 TB/s beside a pass and 3.4
+// alone, so a part that outlasts its pass runs on at less than the regular kernel's rate while the
+// selection waits for it.  32 layers of 32q/8kv heads at 131072 tokens, int8, ms by part:
+//   with pass 1, 64 guide rows 6.47 (2/5) 6.22 (1/5), 128 6.78 6.44, 192 7.00 (2/5) 6.66 (1/5),
+//   256 6.64 to 7.05 (2/5) 6.63 to 6.94 (7/20) 6.70 to 7.00 (3/10) on three cards, 320 10.00 (2/5)
+//   10.16 (3/10), a batch of 206 in the mean 3.53 (2/5) 3.51 (7/20) 3.67 (1/5);
+//   scales only 128 6.16 (1/2) 5.17 (3/10), 192 5.98 5.37, 224 6.10 6.20, 256 6.12 6.20;
+//   normalisers given 128 5.54 (1/2 in 512 workgroups) 4.68 (1/5 in 256), 192 5.78 4.85, 256 5.87
+//   4.95 (3/10 in 256), 512 7.08 (1/2 in 512) 6.81 (1/2 in 256); scales only 32 4.57 (3/5 in
+//   512) 3.93 (1/5 in 256), 96 3.68 3.64, 128 3.86 3.79, 192 3.73 3.91, 256 4.00 4.29.
+// At head_dim 64, where a byte of K has twice the logits, 2/5 and 1/2 hold from 64 rows (3.21 (2/5)
+// 3.33 (1/5) at 64, 4.21 4.42 at 256).
+// For scales only beside pass 2 alone, twice as many workgroups as there are CUs: the second of each
+// starts as pass 2 leaves its CU, where one workgroup per CU moves 3.4 TB/s only (3/5 at 256 rows
+// 4.00, 2/5 in 256 workgroups 4.07); with codes, and with pass 1, they take a CU from pass 2's
+// next workgroup (5.11 -> 5.26 at 256 rows, 6.67 -> 6.96).
+struct Step2Split {
+  int64_t num, den;      // the lean part of all rows, per pass
+  unsigned lean_blocks;  // beside pass 2
+};
+static Step2Split step2_split(const tp_batch* bt, int64_t R, int32_t head_dim, bool pass1, bool codes) {
+  const unsigned one = tp::kLeanBlocks;
+  double logits = 0.0;
+  for (int b = 0; b < bt->batch; ++b) {
+    const int64_t g = bt->guide_offsets[b + 1] - bt->guide_offsets[b];
+    logits += (double)(bt->ctx_offsets[b + 1] - bt->ctx_offsets[b]) * (double)((R * g + 63) / 64 * 64);
+  }
+  // guide rows (as staged) that a context token meets in the mean
+  const double rows = head_dim == 128 ? logits / (double)bt->ctx_offsets[bt->batch] : INFINITY;
+  if (codes) {
+    if (rows <= 192) return {1, 5, one};
+    if (pass1) return rows <= 256 ? Step2Split{7, 20, one} : Step2Split{2, 5, one};
+    return rows <= 256 ? Step2Split{3, 10, one} : Step2Split{1, 2, one};
+  }
+  if (pass1) return rows <= 192 ? Step2Split{3, 10, one} : Step2Split{1, 2, one};
+  return rows <= 64 ? Step2Split{1, 5, one} : Step2Split{3, 5, 2 * one};
+}
+
 // tp_evict on the caller's stream alone: with `qa`, step 2 between the row normalisers and score
 // pass 2 (which then follows a memory-bound kernel, at a higher clock); without, step 2 was done
 // beforehand, and event [3] (after step 2) follows [2] with no kernel between them.
@@ -819,20 +862,12 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
   // HBM well below the copy rate) and the last part while pass 2 runs; the regular kernel
   // takes the middle part between the normalisers and pass 2, which then starts after a
   // memory-bound kernel instead of right after pass 1, at a higher power-limited clock.
-  // With pass 1 each lean part is 2/5 of the rows (the middle fifth runs alone), or half
-  // when only the scales are written (lighter, so all of it fits beside the passes).  With the
-  // normalisers given there is no pass 1: the regular kernel takes the first half (2/5 for
-  // scales only) and the lean kernel the rest beside pass 2, in twice as many workgroups as there
-  // are CUs, the second of each starting as pass 2 leaves its CU: the lean part outlasts
-  // pass 2, and one workgroup per CU moves 3.4 TB/s only (32 layers, int8 at 131072 tokens 5454
-  // us with the lean part beside the regular one at the start, 5295 beside pass 2 in 256
-  // workgroups, 5181 in 512; scales only 4385, 4277, 4099; int4 at 65536 2394, 2411, 2266).
-  // With pass 1, 512 workgroups take a CU from pass 2's next one (6817 -> 7266 us).
+  // step2_split gives the parts' size.
   // Parts are rounded down to 64 rows.
   const bool pass1 = ga.lse_in == nullptr;
   const bool codes = qa.vq != nullptr;
-  const int64_t num = pass1 ? (codes ? 2 : 1) : (codes ? 1 : 3), den = pass1 ? (codes ? 5 : 2) : (codes ? 2 : 5);
-  const int64_t r_lean = qa.rows * num / den / 64 * 64;
+  const Step2Split split = step2_split(batch, ga.R, dims->head_dim, pass1, codes);
+  const int64_t r_lean = qa.rows * split.num / split.den / 64 * 64;
   const int64_t r_first = pass1 ? r_lean : 0, r_mid_end = qa.rows - r_lean;
   const int64_t vrow = (int64_t)row_bytes_of(qfmt, bits, dims->head_dim);
   auto part = [&](int64_t r0, int64_t r1) {
@@ -861,7 +896,7 @@ tp_status tp_evict(const tp_dims* dims, const tp_batch* batch, const void* q_gui
     hipEvent_t done;
     AuxStream* aux;
     unsigned lean_blocks;
-  } mid{&qa2, &qa3, dims->head_dim, st, ev ? ev[3] : nullptr, aux, pass1 ? tp::kLeanBlocks : 2 * tp::kLeanBlocks};
+  } mid{&qa2, &qa3, dims->head_dim, st, ev ? ev[3] : nullptr, aux, split.lean_blocks};
   auto quant_between = [](void* c) -> hipError_t {
     const Mid* m = (const Mid*)c;
     hipError_t r = tp::launch_quantize(*m->mid, m->head_dim, m->st);

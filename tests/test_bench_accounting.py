@@ -29,15 +29,15 @@ def test_path_bytes_128k():
     q_bytes = w.L * w.Hq * w.g_tot * w.d * 2
     assert path == LH * (644 * n + 780 * k) + q_bytes
     assert abs(path / 1e9 - 24.24) < 0.01
-    # step 2's launches (2/5 of the rows beside each score pass on the second stream, the rest
-    # between the passes) cover every V row once
+    # step 2's launches (7/20 of the rows beside each score pass on the second stream at 256 guide
+    # rows, the rest between the passes) cover every V row once
     row = 2 * w.d + w.d + 4
     assert per["k_quantize"] + 2 * per["k_quantize_lean"] == LH * n * row
-    assert per["k_quantize_lean"] == (LH * n * 2 // 5 // 64 * 64) * row
-    # with the normalisers given: the first half on the second stream, the rest between
+    assert per["k_quantize_lean"] == (LH * n * 7 // 20 // 64 * 64) * row
+    # with the normalisers given: the last 3/10 on the second stream, the rest before pass 2
     per_g, _ = bench.algorithmic_bytes(w, k, normalisers_given=True)
     assert per_g["k_quantize"] + per_g["k_quantize_lean"] == LH * n * row
-    assert per_g["k_quantize_lean"] == (LH * n // 2 // 64 * 64) * row
+    assert per_g["k_quantize_lean"] == (LH * n * 3 // 10 // 64 * 64) * row
     assert bench.LEAN_LAUNCHES == {False: 2, True: 1}
     # scales only: half beside each pass; with the normalisers given, 3/5 on the second stream
     per_s, _ = bench.algorithmic_bytes(w, k, full_codes=False)
@@ -46,6 +46,15 @@ def test_path_bytes_128k():
     assert per_s["k_quantize_lean"] == (LH * n // 2 // 64 * 64) * row_s
     per_gs, _ = bench.algorithmic_bytes(w, k, full_codes=False, normalisers_given=True)
     assert per_gs["k_quantize_lean"] == (LH * n * 3 // 5 // 64 * 64) * row_s
+    # the parts by guide rows a context token meets (4 per guide token here, in 64s): codes two passes,
+    # normalisers given, scales only two passes, normalisers given
+    for g, want in ((16, [(1, 5), (1, 5), (3, 10), (1, 5)]), (17, [(1, 5), (1, 5), (3, 10), (3, 5)]),
+                    (48, [(1, 5), (1, 5), (3, 10), (3, 5)]), (49, [(7, 20), (3, 10), (1, 2), (3, 5)]),
+                    (64, [(7, 20), (3, 10), (1, 2), (3, 5)]), (65, [(2, 5), (1, 2), (1, 2), (3, 5)])):
+        wg = w.with_(guide_lens=(g,))
+        assert [bench.lean_part(wg, c, l) for c in (True, False) for l in (False, True)] == want
+    w64 = w.with_(d=64, guide_lens=(16,))
+    assert [bench.lean_part(w64, c, l) for c in (True, False) for l in (False, True)] == [(2, 5), (1, 2), (1, 2), (3, 5)]
 
 
 def test_path_bytes_scales_only_and_int4():
