@@ -810,7 +810,13 @@ hipError_t launch_pass(const GuideArgs& a, bool attn, hipStream_t stream) {
 
 // One launch per class of sequences that need the same number NP of staged row-block pairs
 // (NP = ceil(min(R G_b, 256) / 64)), so short guides do not pay for 256 rows; each class's
-// arguments give the other sequences empty workgroup ranges.
+// arguments give the other sequences empty workgroup ranges.  Three pairs are padded to four where
+// the call has a class of four anyway and this one is small (at most kPadWgs workgroups of
+// kPadTokens tokens): the fourth pair then costs less than a launch in each pass (tp_guide_scores of
+// two sequences of 1000 tokens, 192 and 256 rows, one layer 44 -> 26 us, 64 layers 72.5 -> 67.8;
+// four of 4000 tokens, 192 rows but the last, 32 layers 246 apart, 253 padded).
+constexpr int64_t kPadWgs = 256, kPadTokens = 2048;
+
 template <int D>
 hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, GuideBetween between, void* ctx) {
   static_assert(kChunkUnit % (32 * kGuideWaves) == 0, "every wave owns whole sub-tiles of a chunk");
@@ -823,13 +829,27 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
     cls[c] = a;
     cls[c].wg_off[0] = 0;
   }
+  const auto pairs_of = [&](int b) {
+    const int64_t rows = (int64_t)a.R * (a.bt.g_off[b + 1] - a.bt.g_off[b]);
+    return (int)(((rows < kRowsPerGroup ? rows : kRowsPerGroup) + 63) / 64);
+  };
+  int64_t wg3 = 0, longest3 = 0;
+  bool four = false;
+  for (int b = 0; b < a.bt.batch; ++b) {
+    const int64_t nb = a.bt.ctx_off[b + 1] - a.bt.ctx_off[b];
+    four = four || pairs_of(b) == 4;
+    if (pairs_of(b) != 3) continue;
+    wg3 += ((int64_t)a.L * a.Hkv * chunks_of(nb, a.chunk) + 7) / 8 * 8;
+    longest3 = std::max(longest3, std::min<int64_t>(nb, seq_chunk(nb, a.chunk)));
+  }
+  const bool pad3 = four && wg3 <= kPadWgs && longest3 <= kPadTokens;
   for (int b = 0; b < a.bt.batch; ++b) {
     const int64_t nb = a.bt.ctx_off[b + 1] - a.bt.ctx_off[b];
     const int64_t gb = a.bt.g_off[b + 1] - a.bt.g_off[b];
     if (nb > max_nb) max_nb = nb;
     if (gb > max_gb) max_gb = gb;
     const int64_t rows = (int64_t)a.R * gb;
-    const int np = (int)(((rows < kRowsPerGroup ? rows : kRowsPerGroup) + 63) / 64);
+    const int np = pairs_of(b) == 3 && pad3 ? 4 : pairs_of(b);
     const int64_t units = (int64_t)a.L * a.Hkv * chunks_of(nb, a.chunk);
     const int64_t seq_wg = (units + 7) / 8 * 8 * ((rows + kRowsPerGroup - 1) / kRowsPerGroup);
     wg[np - 1] += seq_wg;

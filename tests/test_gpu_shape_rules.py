@@ -24,6 +24,11 @@ CHUNK_CASES = [
     # for every number of row blocks, with and without a ragged last sub-tile
     ("tile-counts", 1, 8, 2, 128, [33, 800, 1030, 1290, 1600, 2085], [16, 33, 48, 64, 20, 5], synth.DIST_STUDENT_T3, 5),
     ("tile-counts-64", 1, 8, 2, 64, [2070, 31, 1536, 1056, 511, 768], [64, 48, 16, 33, 20, 5], synth.DIST_NORMAL, 1),
+    # three row-block pairs: without a class of four (launched apart), and beside one with too many
+    # workgroups to be padded to it
+    ("three-pairs", 1, 8, 2, 128, [800, 2085, 33, 1290], [33, 48, 40, 5], synth.DIST_STUDENT_T3, 5),
+    ("three-pairs-64", 1, 8, 2, 64, [1536, 31, 511], [48, 33, 35], synth.DIST_NORMAL, 3),
+    ("three-beside-four", 14, 32, 8, 64, [2600, 70, 300], [40, 64, 5], synth.DIST_NORMAL, 5),
     ("merge-kernel", 14, 32, 8, 64, [513, 70, 300], [64, 130, 5], synth.DIST_NORMAL, 5),  # > 768 workgroups
 ]
 
