@@ -539,8 +539,7 @@ def test_evict_matches_the_four_calls(gpu_lib):
               W.ragged8().with_(name="ragged-fp8", L=2, ctx_lens=(9000, 1, 8193), guide_lens=(32, 128, 7),
                                 keep_budget=500, qfmt=1),
               W.llama8b_32k().with_(name="two-row-groups", L=1, ctx_lens=(5000,), guide_lens=(100,)),
-              # fewer than 192 V rows (the second stream's parts are empty), and a middle part
-              # that is not a whole number of 64-row groups
+              # fewer than 192 V rows, and a number that is not a whole number of 64-row groups
               W.tiny().with_(name="tiny-61-rows", Hq=2, Hkv=1, ctx_lens=(1, 60), guide_lens=(3, 2)),
               W.tiny().with_(name="tiny-401-rows", Hq=4, Hkv=1, ctx_lens=(333, 68), guide_lens=(5, 7)),
               # the pooling fused into the selection: staged windows of the widest staged
@@ -610,9 +609,9 @@ def test_evict_with_supplied_normalisers_against_oracle(gpu_lib):
 
 
 def test_evict_graph_capture(gpu_lib):
-    """tp_evict captured into a graph (its second stream forks from and joins the capturing
-    stream) and replayed several times, with eager work and synchronisations between the
-    replays: every replay gives the eager outputs bit for bit."""
+    """tp_evict captured into a graph (a call small enough for one stream; the overlapped form is
+    captured in test_evict_overlap_line) and replayed several times, with eager work and
+    synchronisations between the replays: every replay gives the eager outputs bit for bit."""
     w = W.ragged8().with_(name="graph-replay", L=2, ctx_lens=(3000, 1, 4097), guide_lens=(32, 5, 64),
                           keep_budget=300)
     pu.log(f"tp_evict graph capture and replay: {w.describe()}")
@@ -646,8 +645,8 @@ def test_evict_graph_capture(gpu_lib):
 
 def test_evict_concurrent_threads(gpu_lib):
     """Two host threads calling tp_evict at the same time, each on its own stream with its
-    own buffers (the calls share the device's second stream and events, whose use is
-    serialised by a lock while enqueueing): every result equals the serial call's."""
+    own buffers (calls small enough for one stream; test_evict_overlapped_threads covers those
+    that share the device's second stream): every result equals the serial call's."""
     import threading
 
     w = W.ragged8().with_(name="threads", L=2, ctx_lens=(3000, 1, 4097), guide_lens=(32, 5, 64), keep_budget=300)
@@ -690,8 +689,8 @@ def test_evict_concurrent_threads(gpu_lib):
 def test_evict_without_full_codes(gpu_lib):
     """tp_evict with v_q = NULL (the kept rows are quantised during the compaction): the
     compact cache, kept set and scores are bit-identical to the run that writes every code,
-    with the normalisers computed and with them supplied (each mode splits step 2 between the
-    two streams differently)."""
+    with the normalisers computed and with them supplied (calls small enough for one stream;
+    test_evict_overlapped_forms covers the overlapped ones)."""
     for w in (W.tiny().with_(name="tiny-int4", bits=4),
               W.ragged8().with_(name="ragged-fp8-nocodes", L=2, ctx_lens=(9000, 1, 8193), guide_lens=(32, 128, 7),
                                 keep_budget=500, qfmt=1)):

@@ -106,6 +106,24 @@ def test_pooling_inside_selection(gpu_lib, lens, pool):
         assert torch.equal(getattr(a, name), getattr(b, name)), name
 
 
+# The pooled one-workgroup selection in its larger register classes (16384, 32768 and 65536 tokens,
+# whose pooling exchanges neighbours across lanes and waves), and its 256-thread class of more than 256
+# short segments: (layers, KV heads, lengths).
+POOLED_CLASSES = [(1, 2, [12000, 8195]), (1, 2, [32767, 17003]), (1, 2, [40001, 300]), (1, 2, [57341, 1]),
+                  (2, 8, [65533, 9]), (8, 4, [57346]), (22, 4, [4093, 77, 1300])]
+
+
+@pytest.mark.parametrize("L,Hkv,lens", POOLED_CLASSES, ids=lambda v: str(v).replace(", ", "-"))
+@pytest.mark.parametrize("pool", [1, 3, 5, 7, 9])
+def test_pooling_inside_selection_classes(gpu_lib, L, Hkv, lens, pool):
+    w = W.Workload("pool", L, 4 * Hkv, Hkv, 64, tuple(lens), (70,) * len(lens), synth.Stream(82, synth.TAG_Q),
+                   synth.Stream(82, synth.TAG_K), synth.Stream(82, synth.TAG_V), keep_ratio=0.2, pool_k=pool)
+    q, k, v = pu.device_inputs(w)
+    a, b = pu.run_gpu(w, q, k, v, fused=True), pu.run_gpu(w, q, k, v, fused=False)
+    for name in ("s_key", "s_comb", "scales", "kept_idx", "k_c", "v_q_c", "scales_c"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+
+
 # tp_evict's second stream: V just below and just above each line (with pass 1; normalisers given),
 # bit for bit the separate calls, the overlapped ones also under capture and replayed.
 @pytest.mark.parametrize("given_lse,full_codes,heads", [(False, True, 79), (False, True, 80), (False, False, 80),
@@ -142,6 +160,115 @@ def test_evict_overlap_line(gpu_lib, given_lse, full_codes, heads):
         torch.cuda.synchronize()
         for name in names:
             assert torch.equal(getattr(got, name), getattr(ref, name)), name
+
+
+OVERLAP_NAMES = ("s_key", "s_comb", "scales", "kept_idx", "k_c", "v_q_c", "scales_c", "v_q")
+
+
+def _overlap_workload(L, Hq, Hkv, d, lens, glens, **kw):
+    w = W.Workload("overlap", L, Hq, Hkv, d, tuple(lens), tuple(glens), synth.Stream(93, synth.TAG_Q),
+                   synth.Stream(93, synth.TAG_K, synth.DIST_STUDENT_T3), synth.Stream(93, synth.TAG_V), keep_ratio=0.1,
+                   **kw)
+    assert w.L * w.Hkv * w.n_tot * w.d * 2 >= 640 << 20  # the second stream is used
+    return w
+
+
+# The overlapped step 2 in each code format, both head sizes, every size of its parts (by the guide
+# rows a token meets) and ragged batches whose parts begin and end inside a segment: (layers, query
+# heads, KV heads, head_dim, context lengths, guide lengths, options).
+OVERLAP_CASES = {
+    "int4-ragged": (3, 16, 8, 128, [60001, 30003, 20007], [9, 70, 33], dict(bits=4)),
+    "int5-256-rows": (1, 64, 16, 128, [90001, 74001], [60, 64], dict(bits=5)),  # 7/20 beside each pass
+    "int2-short-guide": (2, 16, 16, 128, [82001], [48], dict(bits=2)),
+    "e4m3-long-guide": (2, 32, 8, 128, [100003, 64001], [80, 65], dict(qfmt=1)),  # 2/5 beside each pass
+    "int8-d64": (4, 16, 16, 64, [50001, 32003], [16, 5], dict()),
+    "int4-d64": (4, 16, 16, 64, [82005], [40], dict(bits=4)),
+    "int6-d64": (4, 16, 16, 64, [82005], [3], dict(bits=6)),
+    "e4m3-d64": (4, 16, 16, 64, [41001, 41003], [7, 7], dict(qfmt=1)),
+    "norm-add": (2, 32, 16, 128, [82005], [20], dict(rule=1)),
+    "harmonic-wide-pool": (2, 32, 16, 128, [50001, 32004], [20, 90], dict(rule=2, pool_k=13)),
+}
+
+
+@pytest.mark.parametrize("guide_keys,full_codes", [(False, True), (True, False)])
+@pytest.mark.parametrize("name", OVERLAP_CASES)
+def test_evict_overlapped_forms(gpu_lib, name, guide_keys, full_codes):
+    *shape, kw = OVERLAP_CASES[name]
+    w = _overlap_workload(*shape, **kw)
+    q, k, v = pu.device_inputs(w)
+    kg = pu.device_guide_keys(w) if guide_keys else None
+    d, bt = B.dims(w.L, w.Hq, w.Hkv, w.d), B.Batch(w.ctx_offsets(), w.guide_offsets())
+    opts = dict(softmax_scale=w.softmax_scale, pool_k=w.pool_k, qfmt=w.qfmt, bits=w.bits, rule=w.rule, keep_ratio=0.1,
+                k_guide=kg)
+    ref = B.evict(d, bt, q, k, v, **opts)
+    got = B.evict_fused(d, bt, q, k, v, full_codes=full_codes, **opts)
+    torch.cuda.synchronize()
+    for n in OVERLAP_NAMES if full_codes else OVERLAP_NAMES[:-1]:
+        assert torch.equal(getattr(got, n), getattr(ref, n)), n
+
+
+# With the normalisers given the line is 1 GB of V; parts of 1/5, 3/10 and 1/2 beside pass 2, and for
+# scales only 1/5 in one workgroup per CU and 3/5 in two.
+@pytest.mark.parametrize("full_codes", [True, False])
+@pytest.mark.parametrize("name,lens,glens,kw", [("int4", [131073, 131077], [9, 17], dict(bits=4)),
+                                                ("e4m3-256-rows", [262147], [64], dict(qfmt=1)),
+                                                ("int7-long-guide", [200001, 62147], [70, 90], dict(bits=7)),
+                                                ("d64", [262147, 262145], [16, 16], dict(d=64))])
+def test_evict_overlapped_given_normalisers(gpu_lib, name, lens, glens, kw, full_codes):
+    kw = dict(kw)
+    w = _overlap_workload(2, 32, 8, kw.pop("d", 128), lens, glens, **kw)
+    assert w.L * w.Hkv * w.n_tot * w.d * 2 >= 1 << 30
+    q, k, v = pu.device_inputs(w)
+    d, bt = B.dims(w.L, w.Hq, w.Hkv, w.d), B.Batch(w.ctx_offsets(), w.guide_offsets())
+    opts = dict(softmax_scale=w.softmax_scale, pool_k=w.pool_k, qfmt=w.qfmt, bits=w.bits, keep_ratio=0.1)
+    lse = torch.linspace(9.0, 12.0, w.L * w.Hq * w.g_tot, device="cuda")
+    got = B.evict_fused(d, bt, q, k, v, guide_lse=lse, full_codes=full_codes, **opts)
+    ref = B.EvictBuffers(d, bt, w.qfmt, w.bits, got.kept_offsets)
+    B.tp_guide_scores_lse(d, bt, q, k, lse, w.softmax_scale, w.pool_k, ref.s_key, ref.ws_evict)
+    B.tp_quantize_v_scales(d, bt, v, w.qfmt, w.bits, ref.scales, ref.v_q)
+    B.tp_combine_select_topk(d, bt, ref.s_key, ref.scales, w.rule, 0.1, 0, ref.kept_offsets, ref.kept_idx, ref.s_comb)
+    B.tp_compact_kv(d, bt, ref.kept_offsets, ref.kept_idx, k, ref.v_q, ref.scales, w.qfmt, w.bits, ref.k_c, ref.v_q_c,
+                    ref.scales_c)
+    torch.cuda.synchronize()
+    for n in OVERLAP_NAMES if full_codes else OVERLAP_NAMES[:-1]:
+        assert torch.equal(getattr(got, n), getattr(ref, n)), n
+
+
+def test_evict_overlapped_threads(gpu_lib):
+    """Two host threads with overlapped calls at the same time, each on its own stream with its own
+    buffers: the calls share the device's second stream and events, whose use a lock serialises
+    while enqueueing; every result equals the separate calls'."""
+    import threading
+
+    w = _overlap_workload(1, 80, 80, 128, [32769], [8])
+    q, k, v = pu.device_inputs(w)
+    d, bt = B.dims(w.L, w.Hq, w.Hkv, w.d), B.Batch(w.ctx_offsets(), w.guide_offsets())
+    opts = dict(softmax_scale=w.softmax_scale, pool_k=w.pool_k, qfmt=w.qfmt, bits=w.bits, keep_ratio=0.1)
+    ref = B.evict(d, bt, q, k, v, **opts)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    bufs = [B.EvictBuffers(d, bt, w.qfmt, w.bits, ref.kept_offsets) for _ in streams]
+    for st in streams:
+        st.wait_stream(torch.cuda.current_stream())
+    errors = []
+
+    def worker(i):
+        try:
+            for _ in range(4):
+                B.evict_fused(d, bt, q, k, v, bufs=bufs[i], stream=streams[i], **opts)
+            streams[i].synchronize()
+        except Exception as e:  # reported below
+            errors.append(e)
+
+    threads = [threading.Thread(target=worker, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    torch.cuda.synchronize()
+    for b in bufs:
+        for n in OVERLAP_NAMES:
+            assert torch.equal(getattr(b, n), getattr(ref, n)), n
 
 
 # Attention chunks: multiples of 64 tokens in calls of few workgroups, 8192 from three rounds on.  Grids
