@@ -23,9 +23,10 @@ HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak
 FLUSH_BYTES = 512 << 20         # device write between timed steps (larger than every cache)
 
-# The kernels of one tp_evict call, in launch order (the library records an event after each):
+# The kernels of one large tp_evict call, in launch order (the library records an event after each):
 # with the product rule the pooling is part of the selection's first kernel (k_sel_score, which
 # forms the combined scores) and "k_select" is the rest of the selection (four launches).
+# stage_names gives the stages of any call.
 STAGES = ["k_guide_stats", "k_guide_lse", "k_quantize", "k_guide_attn", "k_sel_score", "k_select", "k_compact"]
 KERNEL_SOURCES = {"k_guide_stats": ["guide_scores.hip", "tile_common.h", "tp_internal.h"],
                   "k_guide_lse": ["guide_scores.hip", "tile_common.h", "tp_internal.h"],
@@ -38,8 +39,47 @@ KERNEL_SOURCES = {"k_guide_stats": ["guide_scores.hip", "tile_common.h", "tp_int
                   "k_quantize_lean": ["quantize.hip", "quant_row.h", "quant_recip_table.h", "tp_internal.h", "abi.cpp"],
                   "k_sel_score": ["select.hip", "tp_internal.h", "abi.cpp"],
                   "k_select": ["select.hip", "tp_internal.h", "abi.cpp"],
+                  "k_sel_one": ["select.hip", "tp_internal.h", "abi.cpp"],
                   "k_compact": ["compact.hip", "tp_internal.h"],
                   "k_compact_quant": ["compact.hip", "quant_row.h", "quant_recip_table.h", "tp_internal.h"]}
+
+
+def selects_in_one(w):
+    """Whether one kernel selects each segment (select.hip, one_span): every sequence, with up to 3
+    tokens of misalignment, fits one workgroup, and a pooling window spans adjacent lanes."""
+    from paper_2608_03276_amd import binding as B
+
+    segs = w.L * w.Hkv
+    if w.rule != B.TP_COMBINE_NORM_ADD and w.pool_k // 2 > 4:
+        return False
+    offs = w.ctx_offsets()
+    aligned = (w.n_tot % 4 == 0 or segs == 1) and all(o % 4 == 0 for o in offs[:-1])
+    most = max(w.ctx_lens) + (0 if aligned else 3)
+    return most <= (65536 if segs * w.batch >= 32 else 57344)
+
+
+def step2_overlaps(w, normalisers_given=False):
+    """Whether tp_evict runs part of step 2 on its second stream (abi.cpp, step2_overlaps)."""
+    return w.L * w.Hkv * w.n_tot * w.d * 2 >= (1024 if normalisers_given else 640) << 20
+
+
+def stage_names(w, full_codes=True, normalisers_given=False, step2_done=False):
+    """The kernel (or group of launches) between each two of tp_evict's events, None for none."""
+    from paper_2608_03276_amd import binding as B
+
+    norm_add = w.rule == B.TP_COMBINE_NORM_ADD
+    chunk = 16384 if min(w.ctx_lens) >= 65536 else 8192
+    # pass 2 merges the normalisers itself in calls of up to 768 workgroups; calls of fewer at the
+    # usual chunk may still launch the merge, a few microseconds that are not reported
+    wgs = sum(-(-w.L * w.Hkv * -(-n // chunk) // 8) * 8 * -(-w.R * g // 256) for n, g in zip(w.ctx_lens, w.guide_lens))
+    one = selects_in_one(w)
+    return [None if normalisers_given else "k_guide_stats",
+            None if normalisers_given or wgs <= 768 else "k_guide_lse",
+            None if step2_done else "k_quantize",
+            "k_guide_attn",
+            "k_guide_pool" if norm_add else ("k_sel_one" if one else "k_sel_score"),
+            ("k_sel_one" if one else "k_select") if norm_add else (None if one else "k_select"),
+            "k_compact" if full_codes else "k_compact_quant"]
 
 
 def algorithmic_bytes(w, kept_total_per_head, full_codes=True, normalisers_given=False):
@@ -66,6 +106,7 @@ def algorithmic_bytes(w, kept_total_per_head, full_codes=True, normalisers_given
         "k_quantize": LH * n * (2 * d + rb + 4),                        # read V, write codes and scales
         "k_sel_score": LH * n * (4 + 4 + 4 + 4),                        # read raw, scales; write s_key, S
         "k_select": LH * (n * 4 + kt * 4),                              # read S once more, write kept idx
+        "k_sel_one": LH * (n * (4 + 4 + 4 + 4) + kt * 4),               # k_sel_score and the kept idx
         "k_compact": LH * kt * (2 * (2 * d + rb + 4) + 4),              # read kept rows + idx, write them
         "k_compact_quant": LH * kt * (2 * d + 2 * d + 4 + 2 * d + rb + 4),  # read kept K, V, idx; write
     }
@@ -73,10 +114,15 @@ def algorithmic_bytes(w, kept_total_per_head, full_codes=True, normalisers_given
     if not full_codes:
         per["k_quantize"] = LH * n * (2 * d + 4)                        # read V, write scales
         path = LH * (n * (2 * d + 2 * d + 4) + kt * (2 * d + 2 * d + 4 + 2 * d + rb + 4)) + q_bytes
-    # tp_evict quantises a part of the V rows (rounded down to 64 rows) on its second stream
+    # a large tp_evict quantises a part of the V rows (rounded down to 64 rows) on its second stream
     # beside each score pass (two k_quantize_lean launches), or, with the normalisers given,
     # one part beside pass 2 (one launch); the k_quantize launch timed between the events does the
     # rest.  lean_part gives the part as a fraction of the rows.
+    if w.rule == B.TP_COMBINE_NORM_ADD:  # pooled before: reads s_key and the scales, writes S and the kept idx
+        per["k_sel_one"] = LH * (n * (4 + 4 + 4) + kt * 4)
+        per["k_select"] = LH * (n * (4 + 4 + 4 + 4) + kt * 4)           # and reads S once more
+    if not step2_overlaps(w, normalisers_given):
+        return per, path
     rows = LH * n
     full = per["k_quantize"]
     num, den = lean_part(w, full_codes, normalisers_given)
@@ -458,16 +504,9 @@ def main():
     else:
         step_ms = sorted(e[0].elapsed_time(e[-1]) for e in evs)
     ms = statistics.median(step_ms)
-    stages = STAGES if lse is None else ["pass1_skipped", "lse_given"] + STAGES[2:]
-    if args.no_full_codes:
-        stages = stages[:-1] + ["k_compact_quant"]
-    if w.rule == B.TP_COMBINE_NORM_ADD:  # its norms need the pooled scores first: a pooling kernel
-        stages[4] = "k_guide_pool"
-    stage_ms = {n: statistics.median(e[j].elapsed_time(e[j + 1]) for e in evs) for j, n in enumerate(stages)}
-    for none in ("pass1_skipped", "lse_given"):  # no kernel between these events
-        stage_ms.pop(none, None)
-    if args.prefill_attention:  # step 2 ran inside the attention: no kernel between its events
-        stage_ms.pop("k_quantize")
+    stages = stage_names(w, not args.no_full_codes, lse is not None, args.prefill_attention)
+    stage_ms = {n: statistics.median(e[j].elapsed_time(e[j + 1]) for e in evs) for j, n in enumerate(stages) if n}
+    if args.prefill_attention:
         stage_ms = dict({"k_guide_fwd": statistics.median(a[0].elapsed_time(a[1]) for a in atts)}, **stage_ms)
     timing = {"protocol": f"median of {args.steps} steps, each timed by events at its start and end on the "
                           f"stream it runs on, after {args.warmup} untimed warm-up steps; a {FLUSH_BYTES >> 20} MB "
@@ -514,9 +553,11 @@ def main():
     # summaries were taken on, and while every kernel's sources are unchanged
     measured_path = None
     if same_fmt and kg is None and lse is None and not args.no_full_codes:
-        parts = [measured_traffic(kn, args.workload) for kn in STAGES + ["k_quantize_lean"]]
+        lean = LEAN_LAUNCHES[False] if step2_overlaps(w) else 0
+        parts = [measured_traffic(kn, args.workload) for kn in stages if kn]
+        parts += [measured_traffic("k_quantize_lean", args.workload)] * lean
         if all(p is not None for p in parts):
-            tot = sum(parts) + (LEAN_LAUNCHES[False] - 1) * parts[-1]
+            tot = sum(parts)
             measured_path = {"achieved": round(tot / (ms * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                              "frac": round(tot / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4), "traffic": tot}
     out = {
@@ -550,7 +591,7 @@ def main():
         "stages_ms": {n: round(t, 4) for n, t in stage_ms.items()},
         "kernel_rooflines": {n: {k: v for k, v in roofline_of(n).items()
                                  if k in ("bound", "achieved", "unit", "frac", "other_roof")}
-                             for n in stage_ms if n != "k_guide_lse"},
+                             for n in stage_ms if n != "k_guide_lse" and stage_ms[n] > 0},
     }
     del q, k, v, kg, vg, bufs, flush, ws_attn
     if not args.no_cpu_baseline:

@@ -57,6 +57,36 @@ def test_path_bytes_128k():
     assert [bench.lean_part(w64, c, l) for c in (True, False) for l in (False, True)] == [(2, 5), (1, 2), (1, 2), (3, 5)]
 
 
+def test_stages_follow_the_kernels_that_run():
+    """The stages between tp_evict's events on both sides of the library's lines: the selection of one
+    workgroup per segment, step 2 beside the score passes, the merge of the normalisers."""
+    w = W.llama8b_128k()
+    assert bench.stage_names(w) == bench.STAGES
+    assert bench.stage_names(w, False, True) == [None, None, "k_quantize", "k_guide_attn", "k_sel_score", "k_select",
+                                                 "k_compact_quant"]
+    assert bench.stage_names(W.llama8b_32k()) == bench.STAGES[:4] + ["k_sel_one", None, "k_compact"]
+    assert bench.stage_names(W.llama8b_32k(), True, True, True) == [None, None, None, "k_guide_attn", "k_sel_one", None,
+                                                                   "k_compact"]
+    assert bench.stage_names(W.tiny())[1] is None
+    assert bench.stage_names(W.llama8b_32k().with_(rule=1))[4:6] == ["k_guide_pool", "k_sel_one"]
+    assert bench.stage_names(w.with_(rule=1))[4:6] == ["k_guide_pool", "k_select"]
+    one = lambda lens, **kw: bench.selects_in_one(w.with_(ctx_lens=lens, guide_lens=(8,) * len(lens), **kw))
+    assert one((65536,)) and not one((65537,))                    # 256 segments
+    assert one((65532, 65533)) and one((65533, 65532)) and not one((65534, 65532))  # misaligned segments
+    assert one((57344,), L=1) and not one((57345,), L=1) and one((57345,), L=4)     # 8 and 32 segments
+    assert one((4096,), pool_k=9) and not one((4096,), pool_k=11) and one((4096,), pool_k=11, rule=1)
+    seg = w.L * w.Hkv * w.d * 2
+    for given, line in ((False, 640 << 20), (True, 1024 << 20)):
+        n = line // seg
+        assert bench.step2_overlaps(w.with_(ctx_lens=(n,)), given)
+        below = w.with_(ctx_lens=(n - 1,))
+        assert not bench.step2_overlaps(below, given)
+        per, _ = bench.algorithmic_bytes(below, _kept(below), normalisers_given=given)
+        assert per["k_quantize"] == w.L * w.Hkv * (n - 1) * (2 * w.d + w.d + 4) and "k_quantize_lean" not in per
+    per, _ = bench.algorithmic_bytes(W.llama8b_32k(), 6553)
+    assert per["k_sel_one"] == w.L * w.Hkv * (32768 * 16 + 6553 * 4)
+
+
 def test_path_bytes_scales_only_and_int4():
     w = W.llama8b_128k()
     k = _kept(w)
