@@ -303,11 +303,13 @@ tp_status tp_compact_quantize_kv(const tp_dims* dims, const tp_batch* batch, con
  * stream, in launch order: [0] before the work, [1] after score pass 1, [2] after the row
  * normalisers, [3] after the V quantisation, [4] after score pass 2, [5] after pooling,
  * [6] after the selection, [7] after the compaction; one kernel runs between consecutive
- * events, except that a step which needs no kernel has none: with guide_lse, none from [0] to
- * [2]; in small calls, where score pass 2 merges the row normalisers itself, none between [1]
- * and [2]; where one kernel pools and selects (contexts of up to 65536 tokens, 57344 with
- * fewer than 32 segments), none between
- * [5] and [6].
+ * events (several where the selection is split), except that a step which needs no kernel has
+ * none: with guide_lse, none from [0] to [2]; in small calls, where score pass 2 merges the row
+ * normalisers itself, none between [1] and [2]; with v == NULL, none between [2] and [3].  Except
+ * under TP_COMBINE_NORM_ADD the selection pools the scores itself: the work between [4] and [5] is
+ * then the selection's first kernel, or all of it, and nothing between [5] and [6], where one
+ * kernel selects a segment (pool_k <= 9, and every sequence of up to 65536 tokens, 57344 when
+ * L * Hkv * batch < 32, up to 3 less where segments do not start on a multiple of 4 tokens).
  * num_events = 0 (or a NULL profile) records none.
  */
 #define TP_EVICT_EVENTS 8

@@ -368,8 +368,9 @@ size_t evict_workspace_bytes(const tp_dims* dims, const tp_batch* batch) {
 
 // The second stream of tp_evict on one device and the events that fork it from, and join it
 // to, the caller's stream (part1: the first part of step 2 on it is done): created by the first
-// tp_evict call on that device that overlaps step 2 and kept until the process ends.  `enqueue` is held while a call enqueues its work, so calls from several
-// threads do not interleave their uses of the events.
+// tp_evict call on that device that overlaps step 2 and kept until the process ends.  `enqueue` is
+// held while a call enqueues its work, so calls from several threads do not interleave their
+// uses of the events.
 struct AuxStream {
   std::mutex enqueue;
   bool ready = false;

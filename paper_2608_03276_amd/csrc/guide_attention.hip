@@ -8,9 +8,9 @@
 // Flash-attention style, split over the context in chunks: one workgroup per (sequence,
 // layer, KV head, chunk, group of <= 256 guide rows), eight waves (two per SIMD, so that one
 // wave's exponentials overlap the other's MFMAs), wave w owning rows 32w .. 32w + 31.  The
-// chunk's (plan_attn_chunk) 32-token sub-tiles of K and V stream through a ring of LDS slots filled by direct
-// global->LDS copies issued several sub-tiles ahead (one barrier per pair of sub-tiles), and every
-// wave reads the whole sub-tile.  Per sub-tile, on v_mfma_f32_32x32x16_bf16:
+// chunk's (plan_attn_chunk) 32-token sub-tiles of K and V stream through a ring of LDS slots
+// filled by direct global->LDS copies issued several sub-tiles ahead (one barrier per pair of
+// sub-tiles), and every wave reads the whole sub-tile.  Per sub-tile, on v_mfma_f32_32x32x16_bf16:
 //   S^T = K Q^T (tokens on M, rows on N): a lane holds one row and 16 of the 32 tokens (its
 //       partner lane 32 apart holds the other 16), so the row's running maximum and sum stay
 //       in the lane pair;

@@ -6,8 +6,8 @@
 //   s_key_i = (1/K) sum_{|t|<=K/2} raw_{i+t}                           (zero-padded pooling)
 // The exact per-row normaliser lse_row needs every logit of the row, so the logits are
 // produced twice (never stored): pass 1 keeps an online (max, sum) per row and chunk,
-// a small kernel (or, in small calls, pass 2) merges the chunks into lse, and pass 2 recomputes the logits and sums the
-// normalised weights per token.  Everything is kept in the log2 domain:
+// a small kernel (or, in small calls, pass 2) merges the chunks into lse, and pass 2 recomputes
+// the logits and sums the normalised weights per token.  Everything is kept in the log2 domain:
 // x' = x * scale * log2(e), exp2(x' - lse2).
 //
 // The contraction over d runs on v_mfma_f32_32x32x16_bf16.  Pass 1 puts tokens on M and
@@ -17,8 +17,8 @@
 // orientations because the A and B operand layouts of the instruction coincide.
 //
 // A workgroup (8 waves, one per CU) takes one chunk of 256 to 16384 tokens (plan_chunk) and one
-// group of <= 256 guide rows.  The group's queries sit in LDS for the whole chunk.  Each wave streams its
-// own 32-token K sub-tiles: an asynchronous global->LDS copy into the wave's private
+// group of <= 256 guide rows.  The group's queries sit in LDS for the whole chunk.  Each wave
+// streams its own 32-token K sub-tiles: an asynchronous global->LDS copy into the wave's private
 // staging buffer runs while the wave computes from registers, so no barrier is needed inside
 // the main loop and the K fragments take no prefetch registers.
 //
@@ -156,7 +156,9 @@ __device__ inline void dma_subtile(const char* kchunk, int t0, int ntok, char* k
 // lane's fixed offset, whose swizzle differs between copies only in piece bit 2, 3 or both
 // (j * kTokPerKB enters swz there), so a whole sub-tile takes a few vector instructions instead
 // of about ninety.  Inline assembly for the scalar-base form; completion is tracked by
-// wait_copies.  One wait state separates the M0 write from the copy that reads it.
+// wait_copies.  One wait state separates the M0 write from the copy that reads it; the base comes from
+// scalar instructions, whose results a copy may use at once (a vector instruction's would need
+// five wait states here, which the compiler does not add before inline assembly).
 template <int D>
 __device__ inline void dma_whole(const char* kchunk, int t0, uint32_t kbuf_lds) {
   using C = Cfg<D>;
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(256) void k_guide_key_stats(GuideArgs a) {
     const int tend = min(nt, j - t0 + 1);  // keys t0 .. j of this tile (none for idle lanes)
     for (int t = part; t < tend; t += kKeyLanes) {
       // fp32 dot product of bf16 pairs (v_dot2_f32_bf16), four independent partial sums
-      float part[4] = {0.f, 0.f, 0.f, 0.f};
+      float dot[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int p = 0; p < D / 8; ++p) {
         const uint4 u = keys[t][p];
@@ -499,10 +501,10 @@ __global__ __launch_bounds__(256) void k_guide_key_stats(GuideArgs a) {
         const uint32_t qw[4] = {qv[p].x, qv[p].y, qv[p].z, qv[p].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          part[e] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qw[e]),
-                                                    __builtin_bit_cast(bf16x2, kw[e]), part[e], false);
+          dot[e] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qw[e]),
+                                                   __builtin_bit_cast(bf16x2, kw[e]), dot[e], false);
       }
-      merge_stats(m, s, ((part[0] + part[1]) + (part[2] + part[3])) * a.c, 1.0f);
+      merge_stats(m, s, ((dot[0] + dot[1]) + (dot[2] + dot[3])) * a.c, 1.0f);
     }
   }
 #pragma unroll
@@ -884,7 +886,7 @@ hipError_t launch_d(const GuideArgs& a, hipStream_t stream, hipEvent_t* ev, Guid
       if (e != hipSuccess) return e;
     }
   }
-  if (a.skip_pool) return hipSuccess;  // the split selection pools the raw sums itself
+  if (a.skip_pool) return hipSuccess;  // the selection pools the raw sums itself
   const auto pgrid = [&](int tile) {
     return dim3((unsigned)((max_nb + tile - 1) / tile), (unsigned)(a.L * a.Hkv), (unsigned)a.bt.batch);
   };
@@ -914,7 +916,10 @@ static int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx
                           int32_t batch, int64_t max_slots) {
   static const int32_t kTargets[] = {16384, 14336, 12288, 10240, 8192, 7168, 6144, 5120, 4096, 3584, 3072,
                                      2560,  2048,  1792,  1536,  1280, 1024, 768,  512,  256};
-  static const double kTokenCost[4] = {0.75, 0.75, 0.8, 1.0};  // by staged row-block pairs: K's bytes bound few rows
+  // by staged row-block pairs: K's bytes bound few rows.  One round of 8192-token chunks at head_dim
+  // 128, us per pass: 107, 110, 128, 138 (and 4096-token ones, half of K in the caches, 47, 51, 59,
+  // 73; at head_dim 64 49, 57, 75, 94).
+  static const double kTokenCost[4] = {0.75, 0.75, 0.8, 1.0};
   const int64_t R = Hq / Hkv, segs = (int64_t)L * Hkv;
   struct Seq {
     uint32_t n;  // context tokens
@@ -948,8 +953,9 @@ static int32_t plan_chunk(int32_t L, int32_t Hq, int32_t Hkv, const int64_t* ctx
     Cost cost{0.0, 0.0};
     for (int i = 0; i < 4; ++i) {
       if (wgs[i] <= 0) continue;
-      // a partly filled last round costs half its length: its workgroups have the HBM and the
-      // power budget to themselves
+      // a partly filled last round costs half its length and half its share: its workgroups have the
+      // HBM and the power budget to themselves (4096-token chunks of 256 rows in 1, 1.25, 1.5, 1.75
+      // and 2 rounds 73, 127, 133, 141, 149 us, of 64 rows 47, 79, 89, 98, 110)
       const double whole = ceil(wgs[i] / kCus), r = whole > 1.0 ? 0.5 * (whole + wgs[i] / kCus) : 1.0;
       cost.rounds += r;
       cost.time += r * (kWgTokens + kTokenCost[i] * longest[i]);
