@@ -42,7 +42,7 @@ constexpr int kAttnWaves = kAttnThreads / 64;
 constexpr double kAttnCus = 256.0;         // workgroups in flight: one per CU
 constexpr double kAttnWgTokens = 270.0;    // a workgroup's fixed work in tokens (30 ns each at 256 rows)
 constexpr double kAttnMergeTokens = 0.008; // writing and merging one row's partial of one chunk, likewise
-constexpr double kAttnSlotTokens = 12.0;   // the merge's latency per chunk, likewise
+constexpr double kAttnSlotTokens = 18.0;   // the merge's latency per chunk, likewise
 constexpr float kAttnLazyLimit = 4294967296.0f;  // 2^32: a lane's 16 terms against a stale maximum
 constexpr int kAttnNoQuant = -1;  // the instance that leaves V's step 2 to its own kernel
 
@@ -642,16 +642,16 @@ static int32_t usual_attn_chunk(const int64_t* ctx_off, int32_t batch) {
 // 8192; calls that give it fewer than three rounds of workgroups (the guide units among them) take
 // the chunk with the least estimated time, where that is under kAttnPlanGain of the usual one's:
 // for 1 to 4 rounds the shortest whose workgroups fit, and its doublings, since every chunk's
-// partial output is written and merged.  The estimate is rough (rounds of whole units), so a small
-// estimated gain is not taken: over 296 random calls, against the usual chunk, 10 were more than
-// 2 % slower at a line of 0.9 (25.2 -> 27.7 us at worst), 6 at 0.8, both 1.53 times faster in the
-// mean.  Nor are contexts up to kAttnPlanMin tokens cut (311 tokens in chunks of 64 13.6 -> 14.4
-// us) or chunks of under kAttnChunkMin made (no call gained by them).  Partials are kept within
-// `budget` bytes, the call's workspace.  The attention with the guide keys, us at 8192 and at the
-// chunk chosen: one layer of 32q/8kv heads, 64 guide tokens, at 17001 tokens 178 -> 43 (640), at
-// 32768 175 -> 58 (1088), at 131072 203 -> 175 (4288); seven segments of 3924 tokens 92 -> 29 (256).
-constexpr double kAttnPlanGain = 0.8;
-constexpr int64_t kAttnPlanMin = 384;
+// partial output is written and merged.  The estimate: rounds (a partly filled last one counts
+// half and its share) x a workgroup's fixed work and longest unit, and the merge.  Over 528 random
+// calls (300 to 250000 tokens) against the usual chunk the choice is 1.41 times faster in the mean
+// and 12 are more than 3 % slower (at most 1.10; with 12 tokens a slot, whole rounds and the
+// guide's length left out, 18 and 1.24).  Chunks of under kAttnChunkMin gain nothing.  Partials
+// are kept within `budget` bytes, the call's workspace.  The attention with the guide keys, us at
+// the usual chunk and at the chunk chosen: one layer of 32q/8kv heads, 64 guide tokens, at 17001
+// tokens 179 -> 45 (768), at 32768 181 -> 58 (1152), at 131072 672 -> 164 (4288), four layers at
+// 32768 198 -> 168 (4736); seven segments of 3924 tokens 94 -> 30 (512).
+constexpr double kAttnPlanGain = 0.95;
 constexpr int kAttnChunkMin = 128;
 
 static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_dim, const int64_t* ctx_off,
@@ -660,7 +660,6 @@ static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_
   int64_t longest = 0;
   for (int b = 0; b < batch; ++b) longest = std::max(longest, ctx_off[b + 1] - ctx_off[b]);
   const int32_t usual = usual_attn_chunk(ctx_off, batch);
-  if (longest <= kAttnPlanMin) return usual;
   struct Cost {
     double time, rounds;
   };
@@ -671,10 +670,11 @@ static int32_t plan_attn_chunk(int32_t L, int32_t Hq, int32_t Hkv, int32_t head_
       const int64_t n = ctx_off[b + 1] - ctx_off[b], rows = R * (g_off[b + 1] - g_off[b]);
       wgs += (double)(segs * (chunks_of<kAttnUnit>(n, target) + 1)) * (double)((rows + kRowsPerGroup - 1) / kRowsPerGroup);
       most = std::max<int64_t>(most, std::min<int64_t>(n, seq_chunk<kAttnUnit>(n, target)));
+      most = std::max<int64_t>(most, g_off[b + 1] - g_off[b]);
     }
-    const double rounds = ceil(wgs / kAttnCus);
+    const double rounds = ceil(wgs / kAttnCus), r = rounds > 1.0 ? 0.5 * (rounds + wgs / kAttnCus) : 1.0;
     const double slots = (double)((longest + target - 1) / target);
-    return Cost{rounds * (kAttnWgTokens + (double)most) + slots * ((double)rows_tot * kAttnMergeTokens + kAttnSlotTokens),
+    return Cost{r * (kAttnWgTokens + (double)most) + slots * ((double)rows_tot * kAttnMergeTokens + kAttnSlotTokens),
                 rounds};
   };
   const Cost at_usual = cost_of(usual);
