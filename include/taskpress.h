@@ -337,9 +337,10 @@ typedef struct tp_profile {
  * In large calls (V of 640 MB or more; 1 GB with guide_lse) step 2 of part of the V rows runs on a
  * second stream of the library's, a fifth to a half of them concurrently with each score pass, or,
  * with guide_lse given, the last fifth to three fifths concurrently with score pass 2 (less for
- * short guides, and where codes are written); smaller calls run everything on `stream`.  The arithmetic is the same, so
- * the results are as for the separate calls.  That stream and four events are created, with
- * default priority, by the first such call on a device and kept until the process ends
+ * short guides, and where codes are written); smaller calls run everything on `stream`.  The
+ * arithmetic is the same, so the results are as for the separate calls.  That stream and four
+ * events are created, with default priority, by the first such call (V of that size) on a device
+ * and kept until the process ends
  * (TP_ERR_HIP if that fails); the work is forked from and joined back to `stream`, so the call
  * stays stream-ordered and may be captured into a graph (once the first large call on the
  * device, which creates the stream, has been made outside capture).  Large calls on one device

@@ -234,11 +234,16 @@ struct AttnUnit {
   int gb, rows, row0, nrows, ntok, slot;
 };
 
-// Workgroup -> unit, by one of two grids (attn_grid).
+// Workgroup -> unit, by one of two grids (kAttnPaddedWgs says which).
 // Padded (nrg_max > 0): chunk (the guide unit last) x segment x (sequence, row group), each dimension
 // as large as its largest sequence needs; workgroups without work end at once.
 // Compact: each sequence owns a contiguous range of ids (wg_off), its segments varying fastest, then
-// its chunks (the guide unit last, or first where it is longer than a chunk), then row groups.
+// its chunks (the guide unit last, or first where it is longer than a chunk), then row groups.  The 8
+// XCDs take consecutive ids in turn, so each gets the same mix of chunks and guide units; with a
+// segment's units adjacent, counts that share a factor with 8 give some XCDs more of the long ones
+// (six layers of 16 sequences, head_dim 64: 506 us against 390), and ids for the chunks and row groups
+// that a shorter sequence lacks each wait for a CU's whole LDS (one layer of 16 sequences of 2178 to
+// 60856 tokens: 425 us against 209).
 __device__ inline bool attn_unit(const AttnArgs& a, AttnUnit& u) {
   const bool keys = a.kg != nullptr, padded = a.nrg_max > 0;
   int b, part = 0;
