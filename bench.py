@@ -153,18 +153,21 @@ LEAN_LAUNCHES = {False: 2, True: 1}
 def lean_part(w, full_codes=True, normalisers_given=False):
     """Rows of each k_quantize_lean launch as a fraction (numerator, denominator) of all rows: the
     rule of tp_evict (abi.cpp, step2_split), by the guide rows (multiples of 64) that a context
-    token meets in the mean."""
-    rows = (sum(n * (-(-w.R * g // 64) * 64) for n, g in zip(w.ctx_lens, w.guide_lens)) / w.n_tot
-            if w.d == 128 else float("inf"))
+    token meets in the mean and those of them beyond 128 in their sequence."""
+    staged = [-(-w.R * g // 64) * 64 for g in w.guide_lens]
+    rows = sum(n * r for n, r in zip(w.ctx_lens, staged)) / w.n_tot
+    spare = sum(n * max(r - 128, 0) for n, r in zip(w.ctx_lens, staged)) / w.n_tot
+    if w.d != 128:
+        rows = spare = float("inf")
     if full_codes:
-        if rows <= 192:
+        if spare <= 64:
             return (1, 5)
         if normalisers_given:
-            return (3, 10) if rows <= 256 else (1, 2)
-        return (7, 20) if rows <= 256 else (2, 5)
+            return (3, 10) if spare <= 128 else (1, 2)
+        return (7, 20) if spare <= 128 else (2, 5)
     if normalisers_given:
         return (1, 5) if rows <= 64 else (3, 5)
-    return (3, 10) if rows <= 192 else (1, 2)
+    return (3, 10) if spare <= 64 else (1, 2)
 
 
 def source_sha256(kernel: str) -> str:

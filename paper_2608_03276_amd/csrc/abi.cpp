@@ -717,14 +717,18 @@ static bool step2_overlaps(int64_t rows, int32_t head_dim, bool pass1) {
 // beside pass 2.  With pass 1 and codes 2/5 each (the middle fifth runs alone between the
 // passes), or half each when only the scales are written (lighter, so all of it fits beside the
 // passes).  With the normalisers given there is no pass 1: the regular kernel takes the first
-// half (2/5 for scales only) and the lean kernel the rest beside pass 2.  Less where the passes are short for
-// K's bytes, few guide rows at head_dim 128: the lean kernel moves 1.6 TB/s beside a pass and 3.4
-// alone, so a part that outlasts its pass runs on at less than the regular kernel's rate while the
-// selection waits for it.  32 layers of 32q/8kv heads at 131072 tokens, int8, ms by part:
+// half (2/5 for scales only) and the lean kernel the rest beside pass 2.  Less where the passes are
+// short for K's bytes, few guide rows at head_dim 128: the lean kernel moves 1.6 TB/s beside a pass
+// and 3.4 alone, so a part that outlasts its pass runs on at less than the regular kernel's rate
+// while the selection waits for it.  Up to about 128 rows a pass is bound by K's bytes and hides
+// little, so what counts is the rows beyond 128 that a context token meets in the mean (`spare`).
+// 32 layers of 32q/8kv heads at 131072 tokens, int8, ms by guide rows and part:
 //   with pass 1, 64 guide rows 6.47 (2/5) 6.22 (1/5), 128 6.78 6.44, 192 7.00 (2/5) 6.66 (1/5),
 //   256 6.64 to 7.05 (2/5) 6.63 to 6.94 (7/20) 6.70 to 7.00 (3/10) on three cards, 320 10.00 (2/5)
-//   10.16 (3/10), a batch of 206 in the mean 3.53 (2/5) 3.51 (7/20) 3.67 (1/5);
-//   scales only 128 6.16 (1/2) 5.17 (3/10), 192 5.98 5.37, 224 6.10 6.20, 256 6.12 6.20;
+//   10.16 (3/10), a batch of 206 in the mean and 108 to spare 3.53 (2/5) 3.51 (7/20) 3.67 (1/5), one
+//   of 183 and 87 1.45 (2/5) 1.47 (7/20) 1.55 (1/5), of 119 and 34 1.24 1.25 1.23;
+//   scales only 128 6.16 (1/2) 5.17 (3/10), 192 5.98 5.37, 224 6.10 6.20, 256 6.12 6.20, a batch of
+//   177 in the mean and 86 to spare 2.77 2.89, of 184 and 60 2.16 2.10;
 //   normalisers given 128 5.54 (1/2 in 512 workgroups) 4.68 (1/5 in 256), 192 5.78 4.85, 256 5.87
 //   4.95 (3/10 in 256), 512 7.08 (1/2 in 512) 6.81 (1/2 in 256); scales only 32 4.57 (3/5 in
 //   512) 3.93 (1/5 in 256), 96 3.68 3.64, 128 3.86 3.79, 192 3.73 3.91, 256 4.00 4.29.
@@ -740,20 +744,23 @@ struct Step2Split {
 };
 static Step2Split step2_split(const tp_batch* bt, int64_t R, int32_t head_dim, bool pass1, bool codes) {
   const unsigned one = tp::kLeanBlocks;
-  double logits = 0.0;
+  // guide rows (as staged) that a context token meets in the mean, and those beyond 128 of a sequence
+  double rows = 0.0, spare = 0.0;
   for (int b = 0; b < bt->batch; ++b) {
-    const int64_t g = bt->guide_offsets[b + 1] - bt->guide_offsets[b];
-    logits += (double)(bt->ctx_offsets[b + 1] - bt->ctx_offsets[b]) * (double)((R * g + 63) / 64 * 64);
+    const int64_t r = (R * (bt->guide_offsets[b + 1] - bt->guide_offsets[b]) + 63) / 64 * 64;
+    const double share = (double)(bt->ctx_offsets[b + 1] - bt->ctx_offsets[b]) / (double)bt->ctx_offsets[bt->batch];
+    rows += share * (double)r;
+    spare += share * (double)std::max<int64_t>(r - 128, 0);
   }
-  // guide rows (as staged) that a context token meets in the mean
-  const double rows = head_dim == 128 ? logits / (double)bt->ctx_offsets[bt->batch] : INFINITY;
+  if (head_dim != 128) rows = spare = INFINITY;
+  constexpr double kTie = 1e-6;  // the shares' rounding
   if (codes) {
-    if (rows <= 192) return {1, 5, one};
-    if (pass1) return rows <= 256 ? Step2Split{7, 20, one} : Step2Split{2, 5, one};
-    return rows <= 256 ? Step2Split{3, 10, one} : Step2Split{1, 2, one};
+    if (spare <= 64.0 + kTie) return {1, 5, one};
+    if (pass1) return spare <= 128.0 + kTie ? Step2Split{7, 20, one} : Step2Split{2, 5, one};
+    return spare <= 128.0 + kTie ? Step2Split{3, 10, one} : Step2Split{1, 2, one};
   }
-  if (pass1) return rows <= 192 ? Step2Split{3, 10, one} : Step2Split{1, 2, one};
-  return rows <= 64 ? Step2Split{1, 5, one} : Step2Split{3, 5, 2 * one};
+  if (pass1) return spare <= 64.0 + kTie ? Step2Split{3, 10, one} : Step2Split{1, 2, one};
+  return rows <= 64.0 + kTie ? Step2Split{1, 5, one} : Step2Split{3, 5, 2 * one};
 }
 
 // tp_evict on the caller's stream alone: with `qa`, step 2 between the row normalisers and score

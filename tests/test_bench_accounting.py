@@ -53,6 +53,11 @@ def test_path_bytes_128k():
                     (64, [(7, 20), (3, 10), (1, 2), (3, 5)]), (65, [(2, 5), (1, 2), (1, 2), (3, 5)])):
         wg = w.with_(guide_lens=(g,))
         assert [bench.lean_part(wg, c, l) for c in (True, False) for l in (False, True)] == want
+    # a batch counts the rows beyond 128 of each sequence: half of the tokens with 64 rows, half with 320
+    mixed = w.with_(ctx_lens=(65536, 65536), guide_lens=(16, 80))
+    assert bench.lean_part(mixed) == (7, 20) and bench.lean_part(mixed, True, True) == (3, 10)
+    assert bench.lean_part(mixed.with_(ctx_lens=(65536, 32768))) == (1, 5)
+    assert bench.lean_part(mixed, False) == (1, 2) and bench.lean_part(W.ragged8()) == (2, 5)
     w64 = w.with_(d=64, guide_lens=(16,))
     assert [bench.lean_part(w64, c, l) for c in (True, False) for l in (False, True)] == [(2, 5), (1, 2), (1, 2), (3, 5)]
 
